@@ -16,123 +16,155 @@ namespace bc {
 
 namespace {
 
-// First position p in [0, k) with idx[p] >= x (k if none), found by a
-// whole wave: each round probes 64 evenly spaced positions
-// of the interval that holds the answer and keeps the one gap between a
-// probe below x and the next, so a round divides the interval by 65.
-__device__ __forceinline__ uint32_t wave_lower_bound(const uint32_t* idx, uint32_t k, uint32_t x) {
-    if (k == 0) return 0;
+// First positions in [0, k) with idx[p] >= x0 and >= x1 (k if none), found
+// by a whole wave, both searches advancing together (their loads are in
+// flight at once): each round probes 64 evenly spaced positions of the
+// interval that holds the answer and keeps the one gap between a probe
+// below x and the next, so a round divides the interval by 65.
+__device__ __forceinline__ void wave_lower_bounds(const uint32_t* idx, uint32_t k, const uint32_t (&x)[2],
+                                                  uint32_t (&at)[2]) {
     const uint32_t lane = (uint32_t)lane_id();
-    uint32_t lo = 0, hi = k;  // the answer lies in [lo, hi]
-    while (hi - lo > 64u) {
-        const uint64_t len = hi - lo;
-        const uint32_t pos = lo + (uint32_t)((len * (lane + 1u)) / 65u);
-        const uint32_t c = (uint32_t)__popcll(__ballot(gp(idx)[pos] < x));
-        const uint32_t nlo = c ? lo + (uint32_t)((len * c) / 65u) + 1u : lo;
-        const uint32_t nhi = c < 64u ? lo + (uint32_t)((len * (c + 1u)) / 65u) : hi;
-        lo = nlo;
-        hi = nhi;
+    uint32_t lo[2] = {0, 0}, hi[2] = {k, k};  // the answers lie in [lo, hi]
+    at[0] = at[1] = 0;
+    if (k == 0) return;
+    while (hi[0] - lo[0] > 64u || hi[1] - lo[1] > 64u) {
+        uint64_t len[2];
+        uint32_t y[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            len[q] = hi[q] - lo[q];
+            const uint32_t pos = lo[q] + (uint32_t)((len[q] * (lane + 1u)) / 65u);
+            y[q] = len[q] > 64u ? gp(idx)[pos] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint32_t c = (uint32_t)__popcll(__ballot(y[q] < x[q]));
+            if (len[q] <= 64u) continue;
+            const uint32_t nlo = c ? lo[q] + (uint32_t)((len[q] * c) / 65u) + 1u : lo[q];
+            const uint32_t nhi = c < 64u ? lo[q] + (uint32_t)((len[q] * (c + 1u)) / 65u) : hi[q];
+            lo[q] = nlo;
+            hi[q] = nhi;
+        }
     }
-    const bool below = lo + lane < hi && gp(idx)[lo + lane < hi ? lo + lane : lo] < x;
-    return lo + (uint32_t)__popcll(__ballot(below));
+    bool below[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        below[q] = lo[q] + lane < hi[q] && gp(idx)[lo[q] + lane < hi[q] ? lo[q] + lane : 0u] < x[q];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) at[q] = lo[q] + (uint32_t)__popcll(__ballot(below[q]));
 }
 
 }  // namespace
 
-// Sparse: entries of tensor t in [lo, hi): one wave per tensor.
+// Sparse packing takes two launches.  part_count leaves in part_off[t] the
+// range's first entry of tensor t (high 32 bits) and its number of entries
+// (low 32 bits) and clears part_off[T]; part_copy_sparse turns the counts
+// into offsets in every workgroup, copies, and counts its finished
+// workgroups in part_off[T]: the last one, when nobody reads the counts any
+// more, writes the offsets over them.  Launches and dependent loads bound
+// both (a BERT-base part is 137 thousand entries, 2.2 MB): with the scan in
+// a launch of its own and each workgroup walking its tensors one by one,
+// searching each again, a pack took 28 us.
 __global__ __launch_bounds__(kBlock) void part_count(const PDesc* __restrict__ p, int T,
                                                      const uint32_t* __restrict__ idx,
                                                      uint64_t* __restrict__ part_off) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) part_off[T] = 0;
     const int t = (int)(blockIdx.x * (kBlock / 64) + wave_id());
     if (t >= T) return;
     const PDesc pd = p[t];
-    const uint32_t* ix = idx + pd.in_off;
-    const uint32_t a = wave_lower_bound(ix, pd.k, pd.lo);
-    const uint32_t b = wave_lower_bound(ix, pd.k, pd.hi);
-    if (lane_id() == 0) part_off[t] = b - a;
+    const uint32_t x[2] = {pd.lo, pd.hi};
+    uint32_t at[2];
+    wave_lower_bounds(idx + pd.in_off, pd.k, x, at);
+    if (lane_id() == 0) part_off[t] = (uint64_t)at[0] << 32 | (uint64_t)(at[1] - at[0]);
 }
 
-// In-place exclusive prefix of T counts into T + 1 offsets: one workgroup,
-// each thread a run of consecutive counts.
-__global__ __launch_bounds__(1024) void part_scan(int T, uint64_t* __restrict__ part_off) {
-    __shared__ uint64_t wsum[16];
-    const uint32_t per = ((uint32_t)T + 1023u) / 1024u;
-    const uint32_t b = threadIdx.x * per;
-    const uint32_t e = b + per < (uint32_t)T ? b + per : (uint32_t)T;
-    uint64_t mine = 0;
-    for (uint32_t i = b; i < e; ++i) mine += part_off[i];
-    // block-wide exclusive scan of `mine`
-    const int lane = lane_id(), w = threadIdx.x >> 6;
-    uint64_t inc = mine;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t y = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += y;
-    }
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    uint64_t before = 0, total = 0;
-    for (int q = 0; q < 16; ++q) {
-        before += q < w ? wsum[q] : 0u;
-        total += wsum[q];
-    }
-    uint64_t run = before + inc - mine;
-    for (uint32_t i = b; i < e; ++i) {
-        const uint64_t c = part_off[i];
-        part_off[i] = run;
-        run += c;
-    }
-    if (threadIdx.x == 0) part_off[T] = total;
-}
-
-// Sparse: copy the packed positions [4096 b, 4096 (b+1)) of the part: the
-// tensors covering them in order, each tensor's range entries rebased.
-constexpr uint32_t kPackSpan = 4096;
+// Each workgroup copies spans of 1024 packed positions, four per thread,
+// whose source each thread finds by itself: a search over the offsets of
+// 256 runs of tensors in LDS, then a walk along the run (one tensor up to
+// 256 tensors).  The grid follows the entries expected of the part, up to
+// two workgroups per compute unit: each reads every tensor's count and adds
+// to one counter (512 workgroups for 134 spans: 11 us, 135: 7 us).
+constexpr uint32_t kPackSpan = 1024;
 
 __global__ __launch_bounds__(kBlock) void part_copy_sparse(const PDesc* __restrict__ p, int T,
                                                            const uint32_t* __restrict__ in_idx,
                                                            const float* __restrict__ in_val,
                                                            uint32_t* __restrict__ out_idx,
-                                                           float* __restrict__ out_val,
-                                                           const uint64_t* __restrict__ part_off) {
-    __shared__ int t0_sh;
-    __shared__ uint32_t first_sh;
-    const uint64_t total = part_off[T];
-    const uint64_t b0 = (uint64_t)blockIdx.x * kPackSpan;
-    if (b0 >= total) return;
-    const uint64_t b1 = b0 + kPackSpan < total ? b0 + kPackSpan : total;
-    if (threadIdx.x == 0) {
-        // last tensor whose part starts at or before b0
-        int lo = 0, hi = T - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (part_off[mid] <= b0) lo = mid; else hi = mid - 1;
-        }
-        t0_sh = lo;
-    }
+                                                           float* __restrict__ out_val, uint64_t* part_off) {
+    __shared__ uint64_t run_off[kBlock];
+    __shared__ uint64_t sh[4];
+    __shared__ int last_sh;
+    const uint32_t per = ((uint32_t)T + kBlock - 1u) / (uint32_t)kBlock;  // tensors of a run
+    const uint32_t t0 = threadIdx.x * per < (uint32_t)T ? threadIdx.x * per : (uint32_t)T;
+    const uint32_t t1 = t0 + per < (uint32_t)T ? t0 + per : (uint32_t)T;
+    uint64_t mine = 0;
+    for (uint32_t t = t0; t < t1; ++t) mine += (uint32_t)part_off[t];
+    uint64_t total;
+    const uint64_t before = block_excl_scan_u64(mine, sh, total);
+    run_off[threadIdx.x] = before;
     __syncthreads();
-    for (int t = t0_sh; t < T && part_off[t] < b1; ++t) {
-        const uint64_t o0 = part_off[t], o1 = part_off[t + 1];
-        const uint64_t s0 = o0 > b0 ? o0 : b0, s1 = o1 < b1 ? o1 : b1;
-        if (s0 >= s1) continue;  // uniform: every thread reads the same offsets
-        const PDesc pd = p[t];
-        __syncthreads();  // the previous tensor is done with first_sh
-        if (threadIdx.x < 64) {
-            const uint32_t f = wave_lower_bound(in_idx + pd.in_off, pd.k, pd.lo);
-            if (threadIdx.x == 0) first_sh = f;
+    for (uint64_t b0 = (uint64_t)blockIdx.x * kPackSpan; b0 < total; b0 += (uint64_t)gridDim.x * kPackSpan) {
+        uint64_t src[kPackSpan / kBlock];
+        uint32_t lo[kPackSpan / kBlock], ix[kPackSpan / kBlock];
+        float va[kPackSpan / kBlock];
+#pragma unroll
+        for (uint32_t r = 0; r < kPackSpan / kBlock; ++r) {
+            uint64_t o = b0 + r * (uint32_t)kBlock + threadIdx.x;
+            if (o >= total) o = total - 1;  // a position to read; not written
+            uint32_t run = 0;               // the last run that starts at or before o
+#pragma unroll
+            for (uint32_t b = kBlock / 2; b >= 1; b >>= 1)
+                if (run_off[run + b] <= o) run += b;
+            uint32_t t = run * per;
+            uint64_t left = o - run_off[run];
+            uint64_t w = part_off[t];
+            while (left >= (uint32_t)w) {
+                left -= (uint32_t)w;
+                w = part_off[++t];
+            }
+            src[r] = p[t].in_off + (w >> 32) + left;
+            lo[r] = p[t].lo;
         }
-        __syncthreads();
-        const uint64_t src0 = pd.in_off + first_sh + (s0 - o0);
-        const uint32_t cnt = (uint32_t)(s1 - s0);
-        for (uint32_t i = threadIdx.x; i < cnt; i += kBlock) {
-            out_idx[s0 + i] = gp(in_idx)[src0 + i] - pd.lo;
-            out_val[s0 + i] = gp(in_val)[src0 + i];
+#pragma unroll
+        for (uint32_t r = 0; r < kPackSpan / kBlock; ++r) {
+            ix[r] = gp(in_idx)[src[r]];
+            va[r] = gp(in_val)[src[r]];
+        }
+#pragma unroll
+        for (uint32_t r = 0; r < kPackSpan / kBlock; ++r) {
+            const uint64_t o = b0 + r * (uint32_t)kBlock + threadIdx.x;
+            if (o < total) {
+                gp(out_idx)[o] = ix[r] - lo[r];
+                gp(out_val)[o] = va[r];
+            }
         }
     }
+    // done with the counts; the last workgroup replaces them.  Only reads
+    // come before this point that it could overtake, and the barrier waits
+    // for their data, so the addition needs no release (which would write
+    // back the L2: 9 us of the kernel's 14)
+    __syncthreads();
+    if (threadIdx.x == 0)
+        last_sh = __hip_atomic_fetch_add((unsigned long long*)part_off + T, 1ull, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT) == (unsigned long long)gridDim.x - 1ull;
+    __syncthreads();
+    if (!last_sh) return;
+    uint64_t run = before;
+    for (uint32_t t = t0; t < t1; ++t) {
+        const uint32_t c = (uint32_t)part_off[t];
+        part_off[t] = run;
+        run += c;
+    }
+    if (threadIdx.x == 0) part_off[T] = total;
 }
 
 // Sign and quantizers (`bits` per element): copy tensor t's range words
-// and its scale; part_off gets the (host-computed) word offsets.
+// and its scale; part_off gets the (host-computed) word offsets.  The
+// workgroups of a column share a tensor in pieces of kPackWords words, eight
+// loads in flight per thread (one workgroup for BERT-base's embedding, 2.9 MB
+// of 8-bit codes, would run on alone long after the others).
+constexpr uint32_t kPackWords = 2048;
+
 __global__ __launch_bounds__(kBlock) void part_copy_words(const PDesc* __restrict__ p, int T, uint32_t bits,
                                                           const uint32_t* __restrict__ in_bits,
                                                           const float* __restrict__ in_scale,
@@ -144,8 +176,20 @@ __global__ __launch_bounds__(kBlock) void part_copy_words(const PDesc* __restric
         // bits per element: the range starts on a word (lo is a multiple of 32)
         const uint32_t nw = (uint32_t)(((uint64_t)(pd.hi - pd.lo) * bits + 31u) / 32u);
         const uint64_t src = pd.in_off + (uint64_t)pd.lo / 32u * bits;
-        for (uint32_t i = threadIdx.x; i < nw; i += kBlock) out_bits[pd.out_off + i] = gp(in_bits)[src + i];
-        if (threadIdx.x == 0) {
+        for (uint64_t b = (uint64_t)blockIdx.y * kPackWords; b < nw; b += (uint64_t)gridDim.y * kPackWords) {
+            uint32_t x[kPackWords / kBlock];
+#pragma unroll
+            for (uint32_t r = 0; r < kPackWords / kBlock; ++r) {
+                const uint64_t i = b + r * (uint32_t)kBlock + threadIdx.x;
+                x[r] = gp(in_bits)[src + (i < nw ? i : b)];
+            }
+#pragma unroll
+            for (uint32_t r = 0; r < kPackWords / kBlock; ++r) {
+                const uint64_t i = b + r * (uint32_t)kBlock + threadIdx.x;
+                if (i < nw) gp(out_bits)[pd.out_off + i] = x[r];
+            }
+        }
+        if (blockIdx.y == 0 && threadIdx.x == 0) {
             out_scale[t] = gp(in_scale)[t];
             part_off[t] = pd.out_off;
             if (t == 0) part_off[T] = total;
@@ -154,20 +198,25 @@ __global__ __launch_bounds__(kBlock) void part_copy_words(const PDesc* __restric
 }
 
 hipError_t launch_pack_part(int word_bits, const PDesc* p, int T, bc_payload_dev in, bc_payload_dev out,
-                            uint64_t* part_off, uint64_t words, uint64_t max_entries, int cus, hipStream_t s) {
+                            uint64_t* part_off, uint64_t words, uint64_t max_words, uint64_t expected, int cus,
+                            hipStream_t s) {
     if (T <= 0) return hipSuccess;
     const uint32_t grid = (uint32_t)(T < 4 * cus ? T : 4 * cus);
     if (word_bits) {
-        hipLaunchKernelGGL(part_copy_words, dim3(grid), dim3(kBlock), 0, s, p, T, (uint32_t)word_bits, in.bits,
-                           in.scale, out.bits, out.scale, part_off, words);
+        // pieces of the longest range, while the grid (mostly idle where the
+        // other tensors are short) stays under 64 workgroups per compute unit
+        uint64_t pieces = (max_words + kPackWords - 1) / kPackWords;
+        if (pieces < 1) pieces = 1;
+        if (pieces > 64u * (uint64_t)cus / grid) pieces = 64u * (uint64_t)cus / grid;
+        hipLaunchKernelGGL(part_copy_words, dim3(grid, (uint32_t)pieces), dim3(kBlock), 0, s, p, T,
+                           (uint32_t)word_bits, in.bits, in.scale, out.bits, out.scale, part_off, words);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(part_count, dim3((T + 3) / 4), dim3(kBlock), 0, s, p, T, in.idx, part_off);
-    hipLaunchKernelGGL(part_scan, dim3(1), dim3(1024), 0, s, T, part_off);
-    const uint64_t blocks = (max_entries + kPackSpan - 1) / kPackSpan;
-    if (blocks)
-        hipLaunchKernelGGL(part_copy_sparse, dim3((uint32_t)blocks), dim3(kBlock), 0, s, p, T, in.idx, in.val,
-                           out.idx, out.val, part_off);
+    uint64_t blocks = expected / kPackSpan + 1;
+    if (blocks > 2u * (uint64_t)cus) blocks = 2u * (uint64_t)cus;
+    hipLaunchKernelGGL(part_copy_sparse, dim3((uint32_t)blocks), dim3(kBlock), 0, s, p, T, in.idx, in.val, out.idx,
+                       out.val, part_off);
     return hipGetLastError();
 }
 

@@ -215,10 +215,11 @@ bool randk_buckets(uint32_t C, uint32_t* S, uint32_t* NB);
 
 // Divisible scheme: pack part j of one payload.  word_bits: 0 for the
 // sparse kinds, else the code bits per element (1 sign, 2, 4, 8); words:
-// the packed words (word kinds); max_entries: an upper bound on the part's
-// entries (sparse), which sizes the copy grid.
+// the packed words (word kinds), max_words: the longest range's; expected: the part's entries (sparse) if
+// every tensor's were spread evenly, which sizes the copy grid.
 hipError_t launch_pack_part(int word_bits, const PDesc* p, int T, bc_payload_dev in, bc_payload_dev out,
-                            uint64_t* part_off, uint64_t words, uint64_t max_entries, int cus, hipStream_t s);
+                            uint64_t* part_off, uint64_t words, uint64_t max_words, uint64_t expected, int cus,
+                            hipStream_t s);
 
 // Work-unit sizes of the aggregate kernels (elements per unit).
 

@@ -74,6 +74,37 @@ def test_pack_part_matches_oracle(kind, empty_part):
             assert np.array_equal(bits(out["val"].cpu().numpy()[:tot]), bits(want["val"])), j
 
 
+@pytest.mark.parametrize("case", ["runs", "skewed", "long_words"])
+def test_pack_part_shapes(case):
+    """Tensor counts past one per thread (runs of tensors, empty ones among
+    them), a part that holds far more entries than its share of the range (the
+    copy's grid walks several spans per workgroup), and word ranges of several
+    pieces with a remainder."""
+    rng = np.random.default_rng(77)
+    kind, ratio = "topk", 0.3
+    if case == "runs":
+        ns = [int(x) for x in rng.integers(0, 300, size=700)]
+        grads = [(rng.standard_normal(n) * 0.01).astype(np.float32) for n in ns]
+    elif case == "skewed":
+        ns = [65, 300001, 7]
+        grads = [(rng.standard_normal(n) * np.where(np.arange(n) < n * 0.35, 1.0, 1e-6)).astype(np.float32) for n in ns]
+    else:
+        kind, ns = "qsgd8", [1, 3 * 4 * 2048 * 4 + 33, 0, 4095, 8192]
+        grads = [(rng.standard_normal(n) * 0.01).astype(np.float32) for n in ns]
+    pay = O.compress_set(kind, ratio, SEED, grads, None)[0]
+    dev = _dev_payload(kind, pay)
+    bounds = [[0] + [min(n, (q * n // 3) // 32 * 32) for q in range(1, 3)] + [n] for n in ns]
+    for j in range(3):
+        out, po = _gpu_pack(kind, ratio, ns, dev, bounds, j)
+        want = O.pack_part_set(kind, ns, pay, bounds, j)
+        assert np.array_equal(po.cpu().numpy(), want["off"]), j
+        tot = int(want["off"][-1])
+        a, b = ("bits", "scale") if kind in WORD_KINDS else ("idx", "val")
+        assert np.array_equal(out[a].cpu().numpy().view(np.uint32)[:tot], want[a]), j
+        m = len(ns) if kind in WORD_KINDS else tot
+        assert np.array_equal(bits(out[b].cpu().numpy()[:m]), bits(want[b])), j
+
+
 @pytest.mark.parametrize("kind", ["topk", "randk", "sign", "terngrad", "qsgd4", "qsgd8"])
 @pytest.mark.parametrize("W", [1, 3, 16, 64])
 def test_aggregate_part_matches_oracle(kind, W):
