@@ -12,16 +12,33 @@
 //             key bits 30..20 per tensor -> exact bin of the k-th key ->
 //             stream pass 2 re-reads v and compacts the candidates (keys at
 //             or above that bin) per 4096-element chunk, in index order.
-//   sampled:  a seeded 1% sample (runs of 64 elements) histogrammed per
-//             tensor -> threshold bin with a margin -> ONE stream pass
-//             writes e_new = v and compacts candidates.  If a tensor ends
-//             with fewer than k candidates, the exact histogram path runs
-//             for that tensor only (reading v back from e_new).
-//   both:     radix select over the candidates only (digits of 11, 10 and
-//             10 bits, histograms in LDS, merged with integer atomics)
-//             finds the k-th key tau and how many tau-ties to keep; a scan
-//             over chunks places each chunk's winners; the emit pass writes
-//             the payload and zeroes e_new at the winners.
+//   sampled:  one workgroup per tensor draws a seeded sample (up to 16384
+//             elements in runs of 16) and takes a threshold with a margin
+//             from it, to 2^-13 of the value -> ONE stream pass writes e_new
+//             and compacts candidates.  Tensors of fewer than 16384 elements
+//             are read whole instead and go by their exact threshold.  If a
+//             tensor ends with fewer than k candidates (or with its k-th key
+//             above the range the sample promised), the exact histogram path
+//             runs for that tensor only.
+//   both:     the pass that compacts the candidates also histograms them in
+//             2048 bins of 2^s keys counted from the threshold; the k-th
+//             candidate's bin A follows, then one pass over the candidates
+//             counts those above bin A in each chunk and histograms the few
+//             inside it by their low s bits, and one workgroup per tensor
+//             finds the k-th key tau from those and places every chunk's
+//             winners (a scan over the chunks); the emit pass writes the
+//             payload and zeroes e_new at the winners.  Keys counted from the
+//             threshold need one pass over the candidates where fixed digits
+//             (11, 10, 10 bits) took three.
+// The sampled stream pass writes +0.0 into e_new already at the candidates
+// far enough above the threshold to be winners (a lower estimate of how many
+// keys lie above still says so): scattered 4-byte stores are what the emit
+// pass is bound by, and up to three quarters of them fall away.  Should such
+// a candidate lose after all, the emit pass writes its v back.
+// BERT-base at 1% (199 tensors, 109.5 M elements): seven launches instead of
+// sixteen, 286 instead of 423 us a call, of which the stream pass, at the
+// memory's rate (6.3 TB/s), takes 208, the threshold 19, the emit pass 15 (51
+// before; 22 instead of 102 under DGC), placing 12 and counting 9.
 // Trimming or topping up to exactly k in the selection order makes the
 // sampled kind return the same entries as the exact kind.
 //
@@ -38,19 +55,36 @@ namespace bc {
 
 namespace {
 
-enum FindMode : int {
-    kFindThrExact = 0,    // histogram of all keys -> bin of the k-th key
-    kFindThrSample = 1,   // histogram of sample keys -> threshold with margin
-    kFindDigit0 = 2,      // candidates' bits 30..20 (sets t_fb if too few)
-    kFindDigit1 = 3,      // bits 19..10
-    kFindDigit2 = 4,      // bits 9..0
-};
-
-constexpr uint32_t kAllCandidatesBelow = 16u * kChunk;  // small tensors skip the sample
-
-__device__ __forceinline__ bool active(const uint32_t* fb, int t, bool fb_only) {
-    return !fb_only || fb[t] != 0u;
+// A tensor's threshold word (t_thr): the threshold key, whose low 10 bits
+// are zero, with the shift s of the candidates' bins in bits 3..0.  t_zero
+// holds the key from which the stream pass writes e_new = +0.0 at once
+// (kNoEarlyZero: nowhere).
+constexpr uint32_t kNoEarlyZero = 0xFFFFFFFFu;
+constexpr uint32_t kExactShift = 10;  // bins of 2^10 keys: bits 30..20 of an exact threshold in 1024 of them
+__device__ __forceinline__ uint32_t thr_key(uint32_t w) { return w & ~0x3FFu; }
+__device__ __forceinline__ uint32_t thr_shift(uint32_t w) { return w & 15u; }
+// Bin of a candidate's key: the last bin takes everything past the range.
+__device__ __forceinline__ uint32_t cand_bin(uint32_t key, uint32_t w) {
+    const uint32_t b = (key - thr_key(w)) >> thr_shift(w);
+    return b < (uint32_t)kBins0 ? b : (uint32_t)kBins0 - 1u;
 }
+
+// Place of a chunk's candidate r (of m) in the chunk's slot of kChunk
+// entries.  Slots are 32 KiB apart, so equal places of all chunks would lie
+// on the same few memory channels; a start that moves on by 256 bytes per
+// chunk spreads the short lists over all of them.  Lists of up to half a
+// slot leave the other half alone (cand_vel).
+__device__ __forceinline__ uint32_t cand_at(uint32_t c, uint32_t m, uint32_t r) {
+    return m <= kChunk / 2 ? (r + 32u * c) & (kChunk / 2 - 1u) : r;
+}
+// A DGC step keeps candidate r's velocity u in the slot's second half, where
+// it has written u = +0.0 early (in chunks of up to kListMax candidates).
+constexpr uint32_t kListMax = 512;  // candidates of a chunk listed in LDS at a time
+__device__ __forceinline__ float* cand_vel(const Ws& ws, uint32_t c, uint32_t r) {
+    return (float*)(ws.t_cand + (size_t)c * kChunk + kChunk / 2) + ((r + 64u * c) & (kChunk / 2 - 1u));
+}
+
+constexpr uint32_t kWholeBelow = 4u * kChunk;  // shorter tensors are read whole, not sampled
 
 // The DGC velocity step of a chunk: td holds u (as the fp32 gradient) and
 // e, tg the step's gradient; u receives fl32(fl32(m * u) + fl32(c * g))
@@ -58,7 +92,7 @@ __device__ __forceinline__ bool active(const uint32_t* fb, int t, bool fb_only) 
 // +0.0 past the tensor's end.
 template <bool kNT>
 __device__ __forceinline__ void load_v_dgc(const TDesc& td, const TDesc& tg, uint32_t j, const DgcFuse& f,
-                                           float u[kEpt], float v[kEpt], uint32_t& valid) {
+                                           float (&u)[kEpt], float (&v)[kEpt], uint32_t& valid) {
     float g[kEpt], e[kEpt];
     load_v<kNT>(tg, j, false, g, valid);
     load_v<kNT>(td, j, false, u, valid);
@@ -80,6 +114,28 @@ __device__ __forceinline__ void load_v_dgc(const TDesc& td, const TDesc& tg, uin
 
 __device__ __forceinline__ float* vel_of(const TDesc& td) { return (float*)const_cast<void*>(td.grad); }
 
+// Add the keys of a thread's valid elements to a block's LDS histogram of
+// bits 30..20.  Zeros (most of a sparse aggregate, which the divisible
+// scheme compresses again; untouched rows of an embedding) are counted per
+// thread: as atomic additions they would all meet in one bin (13.7 M
+// elements, 92% zeros: 53 us, against 12.5 us counted apart).
+__device__ __forceinline__ void add_keys(uint32_t* lh, const float (&v)[kEpt], uint32_t valid) {
+    uint32_t zeros = 0;
+#pragma unroll
+    for (int i = 0; i < kEpt; ++i) {
+        const uint32_t key = key_of(v[i]);
+        if ((valid >> i) & 1u) {
+            if (key != 0u) atomicAdd(&lh[key >> 20], 1u);
+            else ++zeros;
+        }
+    }
+    if (__ballot(zeros != 0u)) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, o, 64);
+        if (lane_id() == 0) atomicAdd(&lh[0], zeros);
+    }
+}
+
 // Flush a block's LDS histogram into the tensor's global histogram.
 __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* gh, int bins) {
     for (int b = threadIdx.x; b < bins; b += kBlock) {
@@ -90,560 +146,914 @@ __device__ __forceinline__ void flush_hist(const uint32_t* lh, uint32_t* gh, int
 
 }  // namespace
 
-// Stream pass of the exact path: e_new = v (when `write_resid`; kDGC: after
-// the velocity step) and the histogram of key bits 30..20.  With `fb_only`
-// it re-reads the stored v of tensors flagged for the fallback.
+// Stream pass of the exact path: e_new = v (kDGC: after the velocity step)
+// and the histogram of key bits 30..20.
 template <bool kDGC>
-__global__ __launch_bounds__(kBlock) void topk_hist_pass(const TDesc* __restrict__ d, int T, uint32_t C,
-                                                         int write_resid, int fb_only, Ws ws,
+__global__ __launch_bounds__(kBlock) void topk_hist_pass(const TDesc* __restrict__ d, int T, uint32_t C, Ws ws,
                                                          uint64_t* __restrict__ clear_status, int copies,
                                                          DgcFuse f) {
     __shared__ uint32_t lh[kBins0];
-    if (fb_only && ws.t_any[0] == 0u) return;  // no tensor fell back
-    for (uint32_t c = blockIdx.x; c < C; c += gridDim.x) {
-        if (clear_status && threadIdx.x == 0) clear_status[c] = 0ull;
-        const int t = tensor_of_chunk(d, T, c);
-        if (!active(ws.t_fb, t, fb_only)) continue;
-        const TDesc td = d[t];
-        const uint32_t j = c - td.chunk0;
-        for (int b = threadIdx.x; b < kBins0; b += kBlock) lh[b] = 0;
-        float v[kEpt];
-        uint32_t valid;
-        if (kDGC && write_resid) {
-            float u[kEpt];
-            load_v_dgc<false>(td, f.dg[t], j, f, u, v, valid);
-            store_chunk(vel_of(td), td.n, j, u);
-            store_chunk(td.resid, td.n, j, v);
-        } else if (write_resid) {
-            load_v(td, j, td.resid != nullptr, v, valid);
-            if (td.resid) store_chunk(td.resid, td.n, j, v);
-        } else {
-            load_stored_v(td, j, v, valid);
-        }
-        __syncthreads();
-        // zeros (most of a sparse aggregate, which the divisible scheme
-        // compresses again; untouched rows of an embedding) are counted per
-        // thread: as atomic additions they would all meet in one bin (13.7 M
-        // elements, 92% zeros: 53 us, against 12.5 us counted apart)
-        uint32_t zeros = 0;
+    const uint32_t c = blockIdx.x;
+    if (clear_status && threadIdx.x == 0) clear_status[c] = 0ull;
+    const int t = tensor_of_chunk(d, T, c);
+    const TDesc td = d[t];
+    const uint32_t j = c - td.chunk0;
+    for (int b = threadIdx.x; b < kBins0; b += kBlock) lh[b] = 0;
+    float v[kEpt];
+    uint32_t valid;
+    if constexpr (kDGC) {
+        float u[kEpt];
+        load_v_dgc<false>(td, f.dg[t], j, f, u, v, valid);
+        store_chunk(vel_of(td), td.n, j, u);
+        store_chunk(td.resid, td.n, j, v);
+    } else {
+        load_v(td, j, td.resid != nullptr, v, valid);
+        if (td.resid) store_chunk(td.resid, td.n, j, v);
+    }
+    __syncthreads();
+    add_keys(lh, v, valid);
+    __syncthreads();
+    flush_hist(lh, ws.t_hist + ((size_t)t * copies + c % (uint32_t)copies) * kBins0, kBins0);
+}
+
+// Thresholds of the sampled kind: one workgroup per tensor looks at up to
+// 16384 elements, kept as keys in registers (16 a thread), and takes from
+// them the threshold and the early-zero key, first to key bits 30..20, then
+// to bits 30..10, with two LDS histograms.  A tensor of fewer than 16384
+// elements is read whole: its threshold is exact to those bits.  A longer one
+// gives 2% of its elements, at least 4096 and at most 16384, in runs of 16
+// (64 bytes of fp32), one at a Philox-drawn place in each of as many equal
+// strata.  (With a histogram of bits 30..20 alone the threshold falls up to
+// an eighth of an octave low; error feedback holds the top 1% of a steady
+// gradient within a few percent of the k-th, so that seven to nine times k
+// entries became candidates, against 1.3 to 2.3 times now.)  The LDS
+// additions bound it, about a cycle each, so four times the elements took
+// twice the time for a margin that the sample does not need.  Also clears the
+// tensor's histograms and, first of all kernels of a call, the fallback's
+// words.
+constexpr int kThrBlock = 1024;
+constexpr uint32_t kThrGroups = kWholeBelow / 4 / kThrBlock;  // groups of 4 elements a thread holds
+constexpr uint32_t kRun = 16;
+constexpr uint32_t kRunsMin = 4096 / kRun, kRunsMax = kWholeBelow / kRun;
+constexpr uint32_t kNoKey = 0xFFFFFFFFu;
+static_assert(kRunsMax <= 4 * kThrBlock && kWholeBelow / 4 / kRunsMin >= kRun / 4, "sampling geometry");
+
+namespace {
+
+// One element as the stream pass will form it.
+template <bool kDGC>
+__device__ __forceinline__ float form_v(float g, float u, float e, bool resid, const DgcFuse& f, float clip) {
+    if constexpr (kDGC) {
+        if (f.clip) g = clip * g;
+        const float mu = f.m * u;
+        g = mu + g;
+    }
+    return resid ? g + e : g;
+}
+
+// Keys of kN groups of 4 elements (first elements at[]), whose loads are all
+// in flight together: kDT and kResid keep them free of branches.
+template <bool kDGC, int kDT, bool kResid, uint32_t kN>
+__device__ __forceinline__ void group_keys(const TDesc& td, const TDesc& tg, const DgcFuse& f, const uint32_t* at,
+                                           uint32_t* key) {
+    const void* grad = kDGC ? tg.grad : td.grad;
+    f32x4 g[kN], e[kN], u[kN];
+    u32x2 h[kN];
 #pragma unroll
-        for (int i = 0; i < kEpt; ++i) {
-            const uint32_t key = key_of(v[i]);
-            if ((valid >> i) & 1u) {
-                if (key != 0u) atomicAdd(&lh[key >> 20], 1u);
-                else ++zeros;
-            }
-        }
-        if (__ballot(zeros != 0u)) {
+    for (uint32_t q = 0; q < kN; ++q) {
+        if constexpr (kDT == 0) g[q] = ldg4f((const float*)grad + at[q]);
+        else h[q] = ldg2u((const uint16_t*)grad + at[q]);
+        if constexpr (kResid) e[q] = ldg4f(td.resid + at[q]);
+        if constexpr (kDGC) u[q] = ldg4f((const float*)td.grad + at[q]);
+    }
+    const float clip = kDGC && f.clip ? *f.clip : 1.f;
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, o, 64);
-            if (lane_id() == 0) atomicAdd(&lh[0], zeros);
-        }
-        __syncthreads();
-        flush_hist(lh, ws.t_hist + ((size_t)(c % (uint32_t)copies) * T + t) * kBins0, kBins0);
-        __syncthreads();
+    for (uint32_t q = 0; q < kN; ++q)
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+            key[4 * q + p] = key_of(form_v<kDGC>(g_elem<kDT>(g[q], h[q], p), kDGC ? u[q][p] : 0.f,
+                                                 kResid ? e[q][p] : 0.f, kResid, f, clip));
+}
+
+template <bool kDGC, uint32_t kN>
+__device__ __forceinline__ void group_keys(const TDesc& td, const TDesc& tg, const DgcFuse& f, const uint32_t* at,
+                                           uint32_t* key) {
+    const uint32_t dtype = kDGC ? tg.dtype : td.dtype;
+    if (kDGC || td.resid) {  // a DGC step has residuals
+        if (dtype == 0) group_keys<kDGC, 0, true, kN>(td, tg, f, at, key);
+        else group_keys<kDGC, 1, true, kN>(td, tg, f, at, key);
+    } else {
+        if (dtype == 0) group_keys<kDGC, 0, false, kN>(td, tg, f, at, key);
+        else group_keys<kDGC, 1, false, kN>(td, tg, f, at, key);
     }
 }
 
-// Seeded sample: each 4096-element chunk of a tensor larger than
-// kAllCandidatesBelow contributes one run of 64 consecutive elements with
-// probability 0.64 (an expected 1% of the tensor).  A workgroup covers 16
-// consecutive chunks, four per wave: lanes 0..3 of a wave draw its four
-// chunks' runs at once, then the wave issues the four runs' loads together;
-// when the 16 chunks all belong to one tensor (the usual case) the keys
-// are binned in LDS first so the global histogram sees one atomic per
-// non-empty bin.
-constexpr uint32_t kSampleChunksPerBlock = 16;
+// Exclusive prefix over the 1024 threads; sh: one entry per wave, not used
+// by the scan before.
+__device__ __forceinline__ uint32_t wide_scan(uint32_t x, uint32_t* sh) {
+    const int lane = lane_id(), w = threadIdx.x >> 6;
+    uint32_t inc = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)inc, o, 64);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) sh[w] = inc;
+    __syncthreads();
+    uint32_t before = 0;
+#pragma unroll
+    for (int q = 0; q < kThrBlock / 64; ++q) before += q < w ? sh[q] : 0u;
+    return before + inc - x;
+}
+
+}  // namespace
 
 template <bool kDGC>
-__global__ __launch_bounds__(kBlock) void topk_sample_hist(const TDesc* __restrict__ d, int T,
-                                                           uint32_t C, uint64_t seed, int copies, Ws ws,
-                                                           DgcFuse f) {
-    uint32_t* gh0 = ws.t_hist + (size_t)(blockIdx.x % (uint32_t)copies) * T * kBins0;  // this workgroup's copy
-    __shared__ uint32_t lh[kBins0];
-    const uint32_t c0 = blockIdx.x * kSampleChunksPerBlock;
-    const uint32_t c1 = (c0 + kSampleChunksPerBlock < C) ? c0 + kSampleChunksPerBlock : C;
-    const int t0 = tensor_of_chunk(d, T, c0);
-    const bool same = tensor_of_chunk(d, T, c1 - 1) == t0;
-    if (same && d[t0].n < kAllCandidatesBelow) return;
-    if (same)
-        for (int b = threadIdx.x; b < kBins0; b += kBlock) lh[b] = 0;
-    __syncthreads();
-    const int lane = lane_id();
-    // lane q < 4: the run of chunk c0 + wave + 4q (start element, tensor; -1: none)
-    uint32_t run_start = 0;
-    int run_t = -1;
-    if (lane < 4) {
-        const uint32_t c = c0 + (uint32_t)wave_id() + 4u * (uint32_t)lane;
-        if (c < c1) {
-            const int t = tensor_of_chunk(d, T, c);
-            const TDesc td = d[t];
-            const uint32_t j = c - td.chunk0;
-            U64x4 ctr = {{(uint64_t)td.tid, (uint64_t)j, 0, 0}};
+__global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restrict__ d, double ratio, uint64_t seed,
+                                                            int copies, uint32_t max_shift, Ws ws, DgcFuse f) {
+    __shared__ uint32_t lh[4 * kBins0];  // four copies of one histogram (lane mod 4), later of two with 1024 bins
+    __shared__ uint32_t start[kRunsMax];  // first group of 4 of each run
+    __shared__ uint32_t sh[3][kThrBlock / 64];
+    __shared__ uint32_t found[5];
+    const int t = blockIdx.x;
+    const TDesc td = d[t];
+    if (t == 0 && threadIdx.x < kAnyWords) ws.t_any[threadIdx.x] = 0u;
+    {
+        u32x4* gh = (u32x4*)(ws.t_hist + (size_t)t * copies * kBins0);
+        for (int b = threadIdx.x; b < copies * kBins0 / 4; b += kThrBlock) gh[b] = u32x4{0u, 0u, 0u, 0u};
+    }
+    if (td.k == 0) return;
+    const TDesc tg = kDGC ? f.dg[t] : td;
+    const bool whole = td.n < kWholeBelow;
+    const uint32_t units = td.n / 4;
+    uint32_t runs = 0;
+    if (!whole) {
+        runs = td.n / (50u * kRun);
+        runs = runs < kRunsMin ? kRunsMin : runs > kRunsMax ? kRunsMax : runs;
+        const uint64_t step = ((uint64_t)units << 16) / runs;  // a stratum, in units of 2^-16 groups
+        if (4u * threadIdx.x < runs) {
+            const U64x4 ctr = {{(uint64_t)td.tid, (uint64_t)threadIdx.x, 0, 0}};
             const U64x4 r = philox4x64_10(ctr, seed, kStreamSample);
-            const uint32_t u = (uint32_t)(r.v[0] >> 32);
-            const uint32_t len = (j + 1 == td.nchunks) ? td.n - j * (uint32_t)kChunk : (uint32_t)kChunk;
-            if (td.n >= kAllCandidatesBelow && u < 2748779069u && len >= 64) {  // 0.64 * 2^32
-                run_start = j * (uint32_t)kChunk + (uint32_t)(r.v[1] % (uint64_t)(len - 63));
-                run_t = t;
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q) {
+                const uint32_t i = 4u * threadIdx.x + q;
+                const uint32_t a = (uint32_t)(step * i >> 16);
+                const uint32_t len = (uint32_t)(step * (i + 1) >> 16) - a;  // at least 16, and a + len <= units
+                if (i < runs) start[i] = a + (uint32_t)(((r.v[q] >> 32) * (len - (kRun / 4 - 1))) >> 32);
             }
         }
     }
-    float v[4];
-    int tq[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        tq[q] = __builtin_amdgcn_readlane(run_t, q);
-        v[q] = 0.f;
-        if (tq[q] < 0) continue;
-        const uint32_t i = (uint32_t)__builtin_amdgcn_readlane((int)run_start, q) + (uint32_t)lane;
-        const TDesc td = d[tq[q]];
-        if constexpr (kDGC) {  // the value the stream pass will form
-            const TDesc tg = f.dg[tq[q]];
-            float g;
-            if (tg.dtype == 0) g = gp((const float*)tg.grad)[i];
-            else g = h2f(gp((const uint16_t*)tg.grad)[i]);
-            if (f.clip) g = *f.clip * g;
-            const float mu = f.m * gp((const float*)td.grad)[i];
-            const float uu = mu + g;
-            v[q] = uu + gp(td.resid)[i];
-        } else {
-            float g;
-            if (td.dtype == 0) g = gp((const float*)td.grad)[i];
-            else g = h2f(gp((const uint16_t*)td.grad)[i]);
-            v[q] = td.resid ? g + gp(td.resid)[i] : g;
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (tq[q] < 0) continue;
-        const uint32_t bin = key_of(v[q]) >> 20;
-        if (same) atomicAdd(&lh[bin], 1u);
-        else atomicAdd(gh0 + (size_t)tq[q] * kBins0 + bin, 1u);
-    }
-    if (!same) return;
+    for (int b = threadIdx.x; b < 4 * kBins0; b += kThrBlock) lh[b] = 0;
+    if (threadIdx.x < 5) found[threadIdx.x] = 0u;
     __syncthreads();
-    flush_hist(lh, gh0 + (size_t)t0 * kBins0, kBins0);
-}
-
-// One workgroup per tensor: read (and clear) the tensor's histogram and
-// pick the bin / digit the mode asks for.
-__global__ __launch_bounds__(kBlock) void topk_find(const TDesc* __restrict__ d, int T, double ratio,
-                                                    int mode, int fb_only, int copies, Ws ws) {
-    __shared__ uint64_t sh[4];
-    __shared__ uint32_t found_bin, found_above, found_total;
-    if (fb_only && ws.t_any[0] == 0u) return;  // no tensor fell back
-    const int t = blockIdx.x;
-    const TDesc td = d[t];
-    if (td.k == 0 || !active(ws.t_fb, t, fb_only)) return;
-    const int bins = (mode == kFindDigit1 || mode == kFindDigit2) ? kBins12 : kBins0;
-    const int per = bins / kBlock;
-    uint32_t* gh = ws.t_hist + (size_t)t * kBins0;
-    const size_t cs = (size_t)T * kBins0;  // between copies
-    // thread i owns bins [bins - (i+1)*per, bins - i*per): thread 0 the top
-    const int hi = bins - threadIdx.x * per;
-    uint32_t h[8];
-    uint32_t mine = 0;
+    const uint32_t groups = whole ? units : runs * (kRun / 4);
+    const uint32_t total = whole ? td.n : runs * kRun;
+    uint32_t key[4 * kThrGroups + 1];  // kNoKey: none
+    constexpr uint32_t kBatch = kDGC ? kThrGroups / 2 : kThrGroups;  // groups loaded together
 #pragma unroll
-    for (int q = 0; q < 8; ++q) h[q] = 0;
-    // every copy's loads issued together (at most 8 copies)
+    for (uint32_t q0 = 0; q0 < kThrGroups; q0 += kBatch) {
+        uint32_t at[kBatch];
+        if (q0 * kThrBlock < groups) {  // places past the last group read it again
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        if (r < copies) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q < per) h[q] += gh[r * cs + hi - 1 - q];
+            for (uint32_t q = 0; q < kBatch; ++q) {
+                uint32_t i = (q0 + q) * kThrBlock + threadIdx.x;
+                i = i < groups ? i : groups - 1u;
+                at[q] = whole ? 4u * i : 4u * (start[i / 4] + i % 4);
+            }
+            group_keys<kDGC, kBatch>(td, tg, f, at, key + 4 * q0);
         }
+#pragma unroll
+        for (uint32_t q = 0; q < kBatch; ++q)
+#pragma unroll
+            for (int p = 0; p < 4; ++p)
+                if ((q0 + q) * kThrBlock + threadIdx.x >= groups) key[4 * (q0 + q) + p] = kNoKey;
+    }
+    key[4 * kThrGroups] = kNoKey;
+    if (whole && threadIdx.x < td.n % 4) {  // past the last whole group
+        const uint32_t i = 4u * units + threadIdx.x;
+        const TDesc& src = kDGC ? tg : td;
+        const float g = src.dtype == 0 ? gp((const float*)src.grad)[i] : h2f(gp((const uint16_t*)src.grad)[i]);
+        const float u = kDGC ? gp((const float*)td.grad)[i] : 0.f;
+        const float e = td.resid ? gp(td.resid)[i] : 0.f;
+        key[4 * kThrGroups] =
+            key_of(form_v<kDGC>(g, u, e, td.resid != nullptr, f, kDGC && f.clip ? *f.clip : 1.f));
+    }
+    uint32_t zeros = 0;  // counted apart: they would all meet in one bin
+    uint32_t* mine = lh + (threadIdx.x & 3);
+#pragma unroll
+    for (uint32_t q = 0; q <= 4 * kThrGroups; ++q) {
+        if (key[q] == 0u) ++zeros;
+        else if (key[q] != kNoKey) atomicAdd(mine + 4u * (key[q] >> 20), 1u);
     }
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        if (r < copies) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q)
-                if (q < per) gh[r * cs + hi - 1 - q] = 0;
-        }
+    for (int o = 32; o >= 1; o >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, o, 64);
+    if (lane_id() == 0 && zeros) {
+        atomicAdd(lh, zeros);
+        atomicAdd(&found[4], zeros);
     }
-#pragma unroll
-    for (int q = 0; q < 8; ++q) mine += q < per ? h[q] : 0u;
-    uint64_t total64;
-    const uint64_t above0 = block_excl_scan_u64(mine, sh, total64);
-    const uint32_t total = (uint32_t)total64;
-    uint32_t target;
-    if (mode == kFindThrExact) {
-        target = td.k;
-    } else if (mode == kFindThrSample) {
-        if (td.n < kAllCandidatesBelow || total == 0) {
-            if (threadIdx.x == 0) ws.t_thr[t] = 0;
-            return;
-        }
-        // k rule on the sample size, plus a margin so that the candidates
-        // usually cover the k-th key of the tensor
+    __syncthreads();
+    // the threshold's place among the keys, and a place that the k-th key
+    // hardly ever lies above: the k rule on the sample's size with margins
+    uint32_t target = td.k, early = 0;
+    if (!whole) {
         const uint64_t ppm = (uint64_t)llround(ratio * 1e6);
         uint64_t ks = ((uint64_t)total * ppm + 999999u) / 1000000u;
         if (ks < 1) ks = 1;
-        uint64_t tg = ks + ks / 4 + 16;
-        target = (uint32_t)(tg < total ? tg : total);
-    } else if (mode == kFindDigit0) {
-        target = td.k;
-        if (total < td.k) {  // too few candidates: exact fallback for this tensor
-            if (threadIdx.x == 0) {
-                ws.t_fb[t] = 1u;
-                atomicOr(ws.t_any, 1u);
-            }
-            return;
-        }
-        // a tensor that fell back keeps its flag (bytecomp_topk_stats counts them)
-        if (threadIdx.x == 0 && !fb_only) ws.t_fb[t] = 0u;
-    } else {
-        target = ws.t_krem[t];
+        const uint64_t tg2 = ks + ks / 4 + 16;
+        target = (uint32_t)(tg2 < total ? tg2 : total);
+        early = ks - ks / 4 > 8 ? (uint32_t)(ks - ks / 4 - 8) : 0u;
     }
-    if (threadIdx.x == 0) found_total = total;
-    uint32_t above = (uint32_t)above0;
+    {
+        // thread i owns bins 2047 - 2i and 2046 - 2i
+        const uint32_t top = (uint32_t)kBins0 - 1u - 2u * threadIdx.x;
+        uint32_t h[2] = {0, 0};
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        if (q < per) {
+        for (int p = 0; p < 4; ++p) {
+            h[0] += lh[4u * top + p];
+            h[1] += lh[4u * (top - 1u) + p];
+        }
+        uint32_t above = wide_scan(h[0] + h[1], sh[0]);
+#pragma unroll
+        for (uint32_t q = 0; q < 2; ++q) {
             if (above < target && target <= above + h[q]) {
-                found_bin = (uint32_t)(hi - 1 - q);
-                found_above = above;
+                found[0] = top - q;
+                found[1] = above;
             }
+            if (early && above < early && early <= above + h[q]) {
+                found[2] = top - q;
+                found[3] = above;
+            }
+            if (!early && above == 0 && h[q]) found[2] = top - q;  // the highest bin with keys
             above += h[q];
         }
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    const uint32_t b = found_bin;
-    switch (mode) {
-        case kFindThrExact:
-        case kFindThrSample:
-            ws.t_thr[t] = b << 20;
-            break;
-        case kFindDigit0:
-            ws.t_prefix[t] = b << 20;
-            ws.t_krem[t] = target - found_above;
-            break;
-        case kFindDigit1:
-            ws.t_prefix[t] |= b << 10;
-            ws.t_krem[t] = target - found_above;
-            break;
-        default:
-            ws.t_prefix[t] |= b;
-            ws.t_krem[t] = target - found_above;
-            break;
+    const uint32_t b0 = found[0], above0 = found[1], b1 = found[2], above1 = found[3], nz = found[4];
+    for (int b = threadIdx.x; b < 4 * kBins0; b += kThrBlock) lh[b] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t q = 0; q <= 4 * kThrGroups; ++q) {
+        if (key[q] == 0u) continue;
+        const uint32_t b = key[q] >> 20, x = 4u * (key[q] >> 10 & 1023u);
+        if (b == b0) atomicAdd(mine + x, 1u);
+        if (early && b == b1) atomicAdd(mine + 4 * kBins12 + x, 1u);
     }
-    (void)found_total;
+    if (threadIdx.x == 0 && nz) {
+        if (b0 == 0) atomicAdd(lh, nz);
+        if (early && b1 == 0) atomicAdd(lh + 4 * kBins12, nz);
+    }
+    if (threadIdx.x < 4) found[threadIdx.x] = 0u;
+    __syncthreads();
+    {
+        const uint32_t bin = (uint32_t)kBins12 - 1u - threadIdx.x;
+        uint32_t h[2] = {0, 0};
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+            h[0] += lh[4u * bin + p];
+            h[1] += lh[4u * (kBins12 + bin) + p];
+        }
+        const uint32_t a0 = above0 + wide_scan(h[0], sh[1]);
+        const uint32_t a1 = above1 + wide_scan(h[1], sh[2]);
+        if (a0 < target && target <= a0 + h[0]) found[0] = bin;
+        if (early && a1 < early && early <= a1 + h[1]) found[1] = bin;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    const uint32_t thr = b0 << 20 | found[0] << 10;
+    uint32_t zero = kNoEarlyZero, span;
+    if (whole) {  // every key past the k-th's 2^10 wins
+        zero = thr + 1024u;
+        span = 1024u;
+    } else if (early) {
+        zero = (b1 << 20 | found[1] << 10) + 1024u;
+        span = 2u * (zero - thr) + 4096u;  // reaches well past the k-th key's likely place
+    } else {
+        span = ((b1 + 2u) << 20) - thr;
+    }
+    uint32_t s = 4;
+    while (s < max_shift && span > ((uint32_t)(kBins0 - 1) << s)) ++s;
+    ws.t_thr[t] = thr | s;
+    ws.t_zero[t] = zero;
 }
 
-// Candidate compaction.  Stream mode (sampled main pass): v = g + e,
-// e_new = v written back (kDGC: after the velocity step, u written back).
-// Re-read mode: v from the residual (or g).  Candidates = valid entries
-// with key >= t_thr[t], compacted in index order into the chunk's slot of
-// t_cand; also the LDS histogram of their key bits 30..20.
-template <bool kNT, bool kDGC>
-__global__ __launch_bounds__(kBlock) void topk_compact(const TDesc* __restrict__ d, int T, uint32_t C,
-                                                       int stream_mode, int fb_only, int copies, Ws ws,
-                                                       DgcFuse f) {
-    __shared__ uint32_t lh[kBins0];
-    __shared__ uint64_t sh[4];
-    if (fb_only && ws.t_any[0] == 0u) return;  // no tensor fell back
-    for (uint32_t c = blockIdx.x; c < C; c += gridDim.x) {
-        const int t = tensor_of_chunk(d, T, c);
-        if (!active(ws.t_fb, t, fb_only)) continue;
-        const TDesc td = d[t];
-        const uint32_t j = c - td.chunk0;
-        for (int b = threadIdx.x; b < kBins0; b += kBlock) lh[b] = 0;
-        float v[kEpt];
-        uint32_t valid;
-        if (kDGC && stream_mode) {
-            float u[kEpt];
-            load_v_dgc<kNT>(td, f.dg[t], j, f, u, v, valid);
-            store_chunk<kNT>(vel_of(td), td.n, j, u);
-            store_chunk<kNT>(td.resid, td.n, j, v);
-        } else if (stream_mode) {
-            load_v<kNT>(td, j, td.resid != nullptr, v, valid);
-            if (td.resid) store_chunk<kNT>(td.resid, td.n, j, v);
-        } else {
-            load_stored_v(td, j, v, valid);
+// Read (and clear) the eight bins under `hi` of a tensor's histogram, all
+// copies added, highest bin first.  Whole vectors: with single words, lanes
+// 32 bytes apart, the clearing stores bound a find (12 us at T = 199).
+__device__ __forceinline__ void take_bins(uint32_t* gh, int hi, int copies, uint32_t (&h)[8]) {
+    constexpr int stride = kBins0, kMax = kGeneralCopiesMax;
+    u32x4 a[kMax], b[kMax];
+#pragma unroll
+    for (int r = 0; r < kMax; ++r) {
+        a[r] = b[r] = u32x4{0u, 0u, 0u, 0u};
+        if (r < copies) {
+            a[r] = ldg4u(gh + r * stride + hi - 4);
+            b[r] = ldg4u(gh + r * stride + hi - 8);
         }
-        const uint32_t thr = ws.t_thr[t];
-        uint32_t pm = 0;
+    }
 #pragma unroll
-        for (int i = 0; i < kEpt; ++i)
-            if (((valid >> i) & 1u) && key_of(v[i]) >= thr) pm |= 1u << i;
-        uint64_t packed = 0;
+    for (int q = 0; q < 8; ++q) h[q] = 0;
 #pragma unroll
-        for (int r = 0; r < kRounds; ++r) packed |= (uint64_t)__popc((pm >> (4 * r)) & 0xFu) << (16 * r);
-        uint64_t tot;
-        const uint64_t pre = block_excl_scan_u64(packed, sh, tot);
-        uint2* out = ws.t_cand + (size_t)c * kChunk;
+    for (int r = 0; r < kMax; ++r) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            h[q] += a[r][3 - q];
+            h[4 + q] += b[r][3 - q];
+        }
+        if (r < copies) {
+            *(BC_GLOBAL u32x4*)(gh + r * stride + hi - 4) = u32x4{0u, 0u, 0u, 0u};
+            *(BC_GLOBAL u32x4*)(gh + r * stride + hi - 8) = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+}
+
+// The exact candidate threshold of a tensor, the bin of the k-th key in its
+// histogram of key bits 30..20, by a whole workgroup.
+__device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh) {
+    const int hi = kBins0 - threadIdx.x * 8;  // thread i owns the i-th eight bins from the top
+    uint32_t h[8];
+    take_bins(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mine += h[q];
+    uint64_t total;
+    uint32_t above = (uint32_t)block_excl_scan_u64(mine, sh, total);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (above < td.k && td.k <= above + h[q]) {
+            ws.t_thr[t] = (uint32_t)(hi - 1 - q) << 20 | kExactShift;
+            ws.t_zero[t] = kNoEarlyZero;  // e_new is already written
+        }
+        above += h[q];
+    }
+}
+
+// The bin of the k-th candidate of a tensor, by a whole workgroup.  False:
+// fewer than k candidates, or the k-th in the last bin (which has no upper
+// edge); an exact threshold meets neither.
+__device__ __forceinline__ bool find_bin(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh,
+                                         uint32_t* found) {
+    const int hi = kBins0 - threadIdx.x * 8;
+    uint32_t h[8];
+    take_bins(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
+    if (threadIdx.x == 0) found[0] = (uint32_t)kBins0 - 1u;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) mine += h[q];
+    uint64_t total;
+    uint32_t above = (uint32_t)block_excl_scan_u64(mine, sh, total);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        if (above < td.k && td.k <= above + h[q]) {
+            found[0] = (uint32_t)(hi - 1 - q);
+            found[1] = above;
+        }
+        above += h[q];
+    }
+    __syncthreads();
+    if (found[0] == (uint32_t)kBins0 - 1u) return false;  // total < k included
+    if (threadIdx.x == 0) {
+        ws.t_prefix[t] = found[0];
+        ws.t_krem[t] = td.k - found[1];
+    }
+    return true;
+}
+
+__global__ __launch_bounds__(kBlock) void topk_find_thr(const TDesc* __restrict__ d, int copies, Ws ws) {
+    __shared__ uint64_t sh[4];
+    const TDesc td = d[blockIdx.x];
+    if (td.k) find_thr(td, (int)blockIdx.x, copies, ws, sh);
+}
+
+__global__ __launch_bounds__(kBlock) void topk_find_bin(const TDesc* __restrict__ d, int copies, Ws ws) {
+    __shared__ uint64_t sh[4];
+    __shared__ uint32_t found[2];
+    const int t = blockIdx.x;
+    const TDesc td = d[t];
+    if (td.k == 0) return;
+    const bool ok = find_bin(td, t, copies, ws, sh, found);
+    if (threadIdx.x != 0) return;
+    ws.t_fb[t] = ok ? 0u : 1u;  // bytecomp_topk_stats counts them
+    if (!ok) atomicOr(ws.t_any, 1u);
+}
+
+// Candidate compaction.  kStream (sampled main pass): v = g + e,
+// e_new = v written back (kDGC: after the velocity step, u written back),
+// +0.0 at the candidates at or above the threshold word's early-zero key.
+// Re-read mode: v from the residual (or g).  Candidates = valid entries
+// with key at or above the threshold, compacted in index order into the
+// chunk's slot of t_cand; also the LDS histogram of their bins.  They pass
+// through a list in LDS, kListMax at a time, so that they are stored side by
+// side and one thread each instead of one of a thread's 16 elements after
+// another.
+struct CompactLds {
+    uint32_t lh[kBins0];
+    uint64_t sh[4];
+    uint2 list[kListMax];
+};
+
+template <bool kNT, bool kDGC, bool kStream>
+__device__ __forceinline__ void compact_chunk(const TDesc& td, int t, uint32_t c, int copies, const Ws& ws,
+                                              const DgcFuse& f, CompactLds& l, float* list_u) {
+    uint32_t* lh = l.lh;
+    uint64_t* sh = l.sh;
+    uint2* list = l.list;
+    const uint32_t j = c - td.chunk0;
+    const uint32_t w = ws.t_thr[t], zero = ws.t_zero[t];
+    const uint32_t thr = thr_key(w);
+    for (int b = threadIdx.x; b < kBins0; b += kBlock) lh[b] = 0;
+    float v[kEpt], u[kEpt];
+    uint32_t valid;
+    if constexpr (kDGC && kStream) {
+        load_v_dgc<kNT>(td, f.dg[t], j, f, u, v, valid);
+    } else if constexpr (kStream) {
+        load_v<kNT>(td, j, td.resid != nullptr, v, valid);
+        if (td.resid) {
+            float e[kEpt];
+#pragma unroll
+            for (int i = 0; i < kEpt; ++i) e[i] = key_of(v[i]) >= zero ? 0.f : v[i];
+            store_chunk<kNT>(td.resid, td.n, j, e);
+        }
+    } else {
+        load_stored_v(td, j, v, valid);
+    }
+    uint32_t pm = 0;
+#pragma unroll
+    for (int i = 0; i < kEpt; ++i)
+        if (((valid >> i) & 1u) && key_of(v[i]) >= thr) pm |= 1u << i;
+    uint64_t packed = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) packed |= (uint64_t)__popc((pm >> (4 * r)) & 0xFu) << (16 * r);
+    uint64_t tot;
+    const uint64_t pre = block_excl_scan_u64(packed, sh, tot);
+    const uint32_t m = (uint32_t)(tot & 0xFFFFu) + (uint32_t)(tot >> 16 & 0xFFFFu) +
+                       (uint32_t)(tot >> 32 & 0xFFFFu) + (uint32_t)(tot >> 48);
+    const bool keep_u = kDGC && kStream && m <= kListMax;
+    uint2* out = ws.t_cand + (size_t)c * kChunk;
+    if constexpr (kDGC && kStream) {
+        if (keep_u) {
+            uint32_t base = 0;
+#pragma unroll
+            for (int r = 0; r < kRounds; ++r) {
+                uint32_t at = base + (uint32_t)((pre >> (16 * r)) & 0xFFFFu);
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    if ((pm >> (4 * r + q)) & 1u) list_u[at++] = u[4 * r + q];
+                base += (uint32_t)((tot >> (16 * r)) & 0xFFFFu);
+            }
+        }
+        float e[kEpt];
+#pragma unroll
+        for (int i = 0; i < kEpt; ++i) {
+            const bool z = keep_u && key_of(v[i]) >= zero;
+            u[i] = z ? 0.f : u[i];
+            e[i] = z ? 0.f : v[i];
+        }
+        store_chunk<kNT>(vel_of(td), td.n, j, u);
+        store_chunk<kNT>(td.resid, td.n, j, e);
+    }
+    for (uint32_t w0 = 0; w0 < m; w0 += kListMax) {  // once for all but dense chunks
         uint32_t base = 0;
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            uint32_t rank = base + (uint32_t)((pre >> (16 * r)) & 0xFFFFu);
+            uint32_t at = base + (uint32_t)((pre >> (16 * r)) & 0xFFFFu) - w0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int i = 4 * r + q;
                 if ((pm >> i) & 1u) {
-                    const uint32_t e = j * (uint32_t)kChunk + 1024u * r + 4u * threadIdx.x + q;
-                    out[rank++] = make_uint2(e, f2u(v[i]));
-                    atomicAdd(&lh[key_of(v[i]) >> 20], 1u);
+                    if (at < kListMax)
+                        list[at] = make_uint2(j * (uint32_t)kChunk + 1024u * r + 4u * threadIdx.x + q, f2u(v[i]));
+                    ++at;
                 }
             }
             base += (uint32_t)((tot >> (16 * r)) & 0xFFFFu);
         }
-        if (threadIdx.x == 0) ws.t_ccount[c] = base;
         __syncthreads();
-        flush_hist(lh, ws.t_hist + ((size_t)(c % (uint32_t)copies) * T + t) * kBins0, kBins0);
-        __syncthreads();
-    }
-}
-
-// Candidate passes.  A chunk holds about 50 candidates at a 1% rate.  The
-// histogram pass gives each workgroup a range of `span` chunks (sized so
-// that about a thousand workgroups remain), paying the clearing and flushing
-// of its LDS histogram once per range; the count and emit passes give each
-// wave one chunk.
-
-// Radix pass over the candidates of a chunk range (at most 16 chunks):
-// histogram of the next digit among candidates whose higher bits match the
-// prefix chosen so far.  A range inside one tensor (the usual case) walks
-// its candidates as one flattened list, every thread's loads in flight
-// together; a range that crosses tensors walks chunk by chunk and flushes
-// the LDS histogram whenever it moves to another tensor.
-constexpr uint32_t kCandSpanMax = 16;
-
-__global__ __launch_bounds__(kBlock) void topk_cand_hist(const TDesc* __restrict__ d, int T, uint32_t C,
-                                                         uint32_t span, int pass, int copies, Ws ws) {
-    __shared__ uint32_t lh[kBins12];
-    __shared__ uint32_t pre[kCandSpanMax + 1];
-    uint32_t* gh0 = ws.t_hist + (size_t)(blockIdx.x % (uint32_t)copies) * T * kBins0;  // this workgroup's copy
-    const int shift = pass == 1 ? 10 : 0;
-    const int match_shift = pass == 1 ? 20 : 10;
-    const uint32_t c0 = blockIdx.x * span;
-    const uint32_t c1 = c0 + span < C ? c0 + span : C;
-    for (int b = threadIdx.x; b < kBins12; b += kBlock) lh[b] = 0;
-    int t = tensor_of_chunk(d, T, c0);
-    if (c1 <= d[t].chunk0 + d[t].nchunks) {
-        // one tensor: candidate counts of the range, then the flattened walk
-        const uint32_t nc = c1 - c0;
-        const uint32_t mine = threadIdx.x < nc ? ws.t_ccount[c0 + threadIdx.x] : 0u;
-        const uint32_t pfx = ws.t_prefix[t] >> match_shift;
-        if (threadIdx.x < 64) {
-            uint32_t inc = mine;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const uint32_t y = __shfl_up(inc, o, 64);
-                if ((int)threadIdx.x >= o) inc += y;
+        const uint32_t nl = m - w0 < kListMax ? m - w0 : kListMax;
+        for (uint32_t i = threadIdx.x; i < nl; i += kBlock) {
+            const uint2 e = list[i];
+            const uint32_t key = e.y & 0x7FFFFFFFu;
+            out[cand_at(c, m, w0 + i)] = e;
+            if constexpr (kDGC) {
+                if (keep_u && key >= zero) *cand_vel(ws, c, w0 + i) = list_u[i];
             }
-            if (threadIdx.x < nc) pre[threadIdx.x + 1] = inc;
-            if (threadIdx.x == 0) pre[0] = 0;
+            atomicAdd(&lh[cand_bin(key, w)], 1u);
         }
         __syncthreads();
-        const uint32_t M = pre[nc];
-        constexpr int kU = 4;  // candidates per thread with loads in flight together
-        for (uint32_t f0 = 0; f0 < M; f0 += kU * kBlock) {
-            uint32_t key[kU];
-#pragma unroll
-            for (int q = 0; q < kU; ++q) {
-                const uint32_t f = f0 + q * kBlock + threadIdx.x;
-                key[q] = 0xFFFFFFFFu;
-                if (f < M) {
-                    uint32_t ci = 0;  // chunk of the range holding flattened entry f
-#pragma unroll
-                    for (uint32_t b = kCandSpanMax / 2; b >= 1; b >>= 1)
-                        if (ci + b <= nc - 1 && pre[ci + b] <= f) ci += b;
-                    key[q] = ws.t_cand[(size_t)(c0 + ci) * kChunk + (f - pre[ci])].y & 0x7FFFFFFFu;
+    }
+    if (threadIdx.x == 0) ws.t_ccount[c] = m;
+    if (m == 0) return;  // uniform; the histogram is untouched
+    flush_hist(lh, ws.t_hist + ((size_t)t * copies + c % (uint32_t)copies) * kBins0, kBins0);
+}
+
+template <bool kNT, bool kDGC, bool kStream>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void topk_compact(
+    const TDesc* __restrict__ d, int T, int copies, Ws ws, DgcFuse f) {
+    __shared__ CompactLds l;
+    __shared__ float list_u[kDGC && kStream ? kListMax : 1];
+    const int t = tensor_of_chunk(d, T, blockIdx.x);
+    const TDesc td = d[t];
+    compact_chunk<kNT, kDGC, kStream>(td, t, blockIdx.x, copies, ws, f, l, list_u);
+}
+
+// The exact path for the tensors that find_bin flagged, in one launch that
+// ends at once when there are none (the usual case).  Workgroups claim chunks
+// one at a time: first every flagged chunk gets back what the stream pass
+// zeroed early and adds its keys to the tensor's histogram of bits 30..20;
+// whoever finishes the last one finds the exact thresholds; then every
+// flagged chunk is compacted again, and whoever finishes the last finds the
+// bins.  A workgroup waits only between the two, when every chunk is claimed
+// by a workgroup that runs and waits for nothing, so the wait ends whatever
+// part of the grid is resident.
+template <bool kDGC>
+__global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict__ d, int T, uint32_t C, int copies,
+                                                        Ws ws) {
+    __shared__ CompactLds l;
+    __shared__ uint32_t claim, found[2];
+    uint32_t* ctl = ws.t_any;  // 1, 2: chunks claimed and done (histogram); 3: thresholds found; 4, 5: as 1, 2 (compaction)
+    if (ctl[0] == 0u) return;
+    const DgcFuse none{nullptr, 0.f, nullptr};
+    for (int phase = 0; phase < 2; ++phase) {
+        for (;;) {
+            if (threadIdx.x == 0) claim = atomicAdd(ctl + 1 + 3 * phase, 1u);
+            __syncthreads();
+            const uint32_t c = claim;
+            if (c >= C) break;
+            const int t = tensor_of_chunk(d, T, c);
+            const TDesc td = d[t];
+            if (ws.t_fb[t] != 0u && phase == 0) {
+                for (int b = threadIdx.x; b < kBins0; b += kBlock) l.lh[b] = 0;
+                const uint32_t m = ws.t_ccount[c], zero = ws.t_zero[t];
+                if (td.resid && (!kDGC || m <= kListMax)) {
+                    for (uint32_t i = threadIdx.x; i < m; i += kBlock) {
+                        const uint2 e = ws.t_cand[(size_t)c * kChunk + cand_at(c, m, i)];
+                        if ((e.y & 0x7FFFFFFFu) >= zero) {
+                            gp(td.resid)[e.x] = u2f(e.y);
+                            if constexpr (kDGC) gp(vel_of(td))[e.x] = *cand_vel(ws, c, i);
+                        }
+                    }
+                }
+                __syncthreads();  // this workgroup re-reads the chunk
+                float v[kEpt];
+                uint32_t valid;
+                load_stored_v(td, c - td.chunk0, v, valid);
+                add_keys(l.lh, v, valid);
+                __syncthreads();
+                flush_hist(l.lh, ws.t_hist + ((size_t)t * copies + c % (uint32_t)copies) * kBins0, kBins0);
+            } else if (ws.t_fb[t] != 0u) {
+                compact_chunk<false, false, false>(td, t, c, copies, ws, none, l, nullptr);
+            }
+            __threadfence();  // before the chunk counts as done
+            __syncthreads();
+            if (threadIdx.x == 0) claim = atomicAdd(ctl + 2 + 3 * phase, 1u);
+            __syncthreads();
+            const bool last = claim == C - 1u;
+            __syncthreads();
+            if (!last) continue;
+            __threadfence();  // the others' histograms
+            for (int q0 = 0; q0 < T; q0 += kBlock) {
+                const int mine = q0 + (int)threadIdx.x;
+                if (!__syncthreads_or(mine < T && d[mine].k != 0u && ws.t_fb[mine] != 0u)) continue;
+                for (int q = q0; q < T && q < q0 + kBlock; ++q) {
+                    const TDesc tq = d[q];
+                    if (tq.k == 0 || ws.t_fb[q] == 0u) continue;
+                    if (phase == 0) find_thr(tq, q, copies, ws, l.sh);
+                    else (void)find_bin(tq, q, copies, ws, l.sh, found);
+                    __syncthreads();
                 }
             }
-#pragma unroll
-            for (int q = 0; q < kU; ++q)
-                if (key[q] != 0xFFFFFFFFu && (key[q] >> match_shift) == pfx)
-                    atomicAdd(&lh[(key[q] >> shift) & (kBins12 - 1)], 1u);
+            __threadfence();
+            __syncthreads();
+            if (phase == 0 && threadIdx.x == 0)
+                __hip_atomic_store(ctl + 3, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         }
+        if (phase == 1) return;
+        if (threadIdx.x == 0)
+            while (__hip_atomic_load(ctl + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
+                __builtin_amdgcn_s_sleep(8);
         __syncthreads();
-        flush_hist(lh, gh0 + (size_t)t * kBins0, kBins12);
-        return;
+        __threadfence();  // thresholds and restored values written elsewhere
     }
-    __syncthreads();
-    uint32_t prefix = ws.t_prefix[t];
-    uint32_t tend = d[t].chunk0 + d[t].nchunks;
-    for (uint32_t c = c0; c < c1; ++c) {
-        if (c >= tend) {  // next tensor: flush this one's counts
-            __syncthreads();
-            flush_hist(lh, gh0 + (size_t)t * kBins0, kBins12);
-            __syncthreads();
-            for (int b = threadIdx.x; b < kBins12; b += kBlock) lh[b] = 0;
-            __syncthreads();
-            t = tensor_of_chunk(d, T, c);
-            prefix = ws.t_prefix[t];
-            tend = d[t].chunk0 + d[t].nchunks;
-        }
-        const uint32_t m = ws.t_ccount[c];
-        const uint2* cand = ws.t_cand + (size_t)c * kChunk;
-        for (uint32_t i = threadIdx.x; i < m; i += kBlock) {
-            const uint32_t key = cand[i].y & 0x7FFFFFFFu;
-            if ((key >> match_shift) == (prefix >> match_shift))
-                atomicAdd(&lh[(key >> shift) & (kBins12 - 1)], 1u);
-        }
-    }
-    __syncthreads();
-    flush_hist(lh, gh0 + (size_t)t * kBins0, kBins12);
 }
 
-// Per chunk: candidates above tau and equal to tau, counted with ballots;
-// each wave takes kCountChunks consecutive chunks, whose loads it issues
-// together (one chunk per wave for calls of few chunks, where the wave
-// count matters more).
+// Candidates inside the k-th key's bin (a chunk rarely has more than one or
+// two) as one word per chunk: bit 63 set, every one has the low bits in bits
+// 13..0; otherwise up to four of them, 14 bits each.  More, and different
+// ones: the reader goes through the chunk's candidates again.
+constexpr uint32_t kLowsMax = 4;
+constexpr uint64_t kLowsSame = 1ull << 63;
+
+// Per chunk: candidates above the k-th key's bin, and those inside it, which
+// also go into the tensor's histogram of their low s bits.  Each wave takes
+// kCountChunks consecutive chunks, whose loads it issues together (one
+// chunk per wave for calls of few chunks, where the wave count matters
+// more).  Entries with equal low bits are added together, so that a tensor
+// of equal keys costs an addition per chunk and not one per entry.
 constexpr uint32_t kCountBatchFrom = 4096;  // chunks
 
 template <uint32_t kCountChunks>
 __global__ __launch_bounds__(kBlock) void topk_cand_count(const TDesc* __restrict__ d, int T, uint32_t C,
-                                                          Ws ws) {
+                                                          int copies, Ws ws) {
     const int lane = lane_id();
     const uint32_t c0 = (blockIdx.x * (kBlock / 64) + wave_id()) * kCountChunks;
-    uint32_t m[kCountChunks], tau[kCountChunks], key[kCountChunks];
+    uint32_t m[kCountChunks], w[kCountChunks], bin[kCountChunks], key[kCountChunks];
+    int tt[kCountChunks];
 #pragma unroll
-    for (uint32_t u = 0; u < kCountChunks; ++u) m[u] = c0 + u < C ? ws.t_ccount[c0 + u] : 0u;
+    for (uint32_t u = 0; u < kCountChunks; ++u) {
+        m[u] = c0 + u < C ? ws.t_ccount[c0 + u] : 0u;
+        tt[u] = c0 + u < C ? tensor_of_chunk(d, T, c0 + u) : 0;
+    }
 #pragma unroll
-    for (uint32_t u = 0; u < kCountChunks; ++u)
-        tau[u] = c0 + u < C ? ws.t_prefix[tensor_of_chunk(d, T, c0 + u)] : 0u;
-#pragma unroll
-    for (uint32_t u = 0; u < kCountChunks; ++u)
-        key[u] = (uint32_t)lane < m[u] ? ws.t_cand[(size_t)(c0 + u) * kChunk + lane].y & 0x7FFFFFFFu : 0u;
+    for (uint32_t u = 0; u < kCountChunks; ++u) {
+        w[u] = ws.t_thr[tt[u]];
+        bin[u] = ws.t_prefix[tt[u]];
+        key[u] = (uint32_t)lane < m[u]
+                     ? ws.t_cand[(size_t)(c0 + u) * kChunk + cand_at(c0 + u, m[u], (uint32_t)lane)].y & 0x7FFFFFFFu
+                     : 0u;
+    }
 #pragma unroll
     for (uint32_t u = 0; u < kCountChunks; ++u) {
         const uint32_t c = c0 + u;
         if (c >= C) break;
-        const bool in = (uint32_t)lane < m[u];
-        uint32_t gt = (uint32_t)__popcll(__ballot(in && key[u] > tau[u]));
-        uint32_t eq = (uint32_t)__popcll(__ballot(in && key[u] == tau[u]));
         const uint2* cand = ws.t_cand + (size_t)c * kChunk;
-        for (uint32_t i0 = 64; i0 < m[u]; i0 += 64) {  // chunks with more than 64 candidates
-            const uint32_t i = i0 + lane;
-            const uint32_t k2 = i < m[u] ? cand[i].y & 0x7FFFFFFFu : 0u;
-            gt += (uint32_t)__popcll(__ballot(i < m[u] && k2 > tau[u]));
-            eq += (uint32_t)__popcll(__ballot(i < m[u] && k2 == tau[u]));
+        uint32_t* gh = ws.t_hist + (size_t)tt[u] * copies * kBins0;
+        const uint32_t low_mask = (1u << thr_shift(w[u])) - 1u;
+        uint32_t gt = 0, nb = 0;
+        uint32_t cur = 0, cur_n = 0;  // additions to bin `cur` not yet made
+        uint32_t first = 0;
+        bool same = true;
+        uint64_t lows = 0;
+        for (uint32_t i0 = 0; i0 < m[u]; i0 += 64) {
+            const uint32_t i = i0 + (uint32_t)lane;
+            const bool in = i < m[u];
+            uint32_t k = key[u];
+            if (i0) k = in ? cand[cand_at(c, m[u], i)].y & 0x7FFFFFFFu : 0u;
+            const uint32_t b = cand_bin(k, w[u]);
+            gt += (uint32_t)__popcll(__ballot(in && b > bin[u]));
+            const bool inside = in && b == bin[u];
+            const uint32_t low = (k - thr_key(w[u])) & low_mask;
+            uint64_t rest = __ballot(inside);
+            for (int round = 0; rest; ++round) {
+                if (round == 4) {  // many different ones: an addition per entry
+                    if ((rest >> lane) & 1u) atomicAdd(gh + low, 1u);
+                    nb += (uint32_t)__popcll(rest);
+                    same = false;
+                    break;
+                }
+                const uint32_t x = (uint32_t)__builtin_amdgcn_readlane((int)low, (int)__builtin_ctzll(rest));
+                const uint64_t eq = __ballot(inside && low == x) & rest;
+                const uint32_t n = (uint32_t)__popcll(eq);
+                rest &= ~eq;
+                if (nb == 0) first = x;
+                same = same && x == first;
+                for (uint32_t q = nb; q < kLowsMax && q < nb + n; ++q) lows |= (uint64_t)x << (14u * q);
+                nb += n;
+                if (cur_n && x != cur) {
+                    if (lane == 0) atomicAdd(gh + cur, cur_n);
+                    cur_n = 0;
+                }
+                cur = x;
+                cur_n += n;
+            }
         }
         if (lane == 0) {
+            if (cur_n) atomicAdd(gh + cur, cur_n);
             ws.t_gt[c] = gt;
-            ws.t_eq[c] = eq;
+            ws.t_eq[c] = nb;
+            ws.t_off[c] = nb > kLowsMax && same ? kLowsSame | first : lows;
         }
     }
 }
 
-// One workgroup per tensor: place every chunk's winners.  eqb[c] = number
-// of tau-equal candidates in earlier chunks; a chunk keeps its tau-equal
-// candidates while the running count stays below the number needed.  Thread
-// i walks a contiguous run of the tensor's chunks; two block scans over the
-// runs' totals give every chunk its prefix.  Runs of up to kScanRegs chunks
-// (tensors of up to 256 kScanRegs chunks) are read once into registers, all
-// loads in flight together; longer runs are read three times,
-// kScanBatch chunks at a time.
-constexpr uint32_t kScanRegs = 32;
-constexpr uint32_t kScanBatch = 8;
+// One workgroup per tensor: the k-th key tau from the histogram of low bits,
+// then every chunk's place.  eqb[c] = number of tau-equal candidates in
+// earlier chunks; a chunk keeps its tau-equal candidates while the running
+// count stays below the number needed.  Thread i walks a contiguous run of
+// the tensor's chunks; two block scans over the runs' totals give every
+// chunk its prefix.  Runs of up to kPlaceRegs chunks (tensors of up to
+// 1024 kPlaceRegs chunks) keep their counts in registers; longer runs are
+// gone through three times.
+constexpr int kPlaceBlock = kThrBlock;
+constexpr uint32_t kPlaceRegs = 8;
 
 namespace {
-// Winners of one chunk given the tau-equal candidates before it.
-__device__ __forceinline__ uint64_t chunk_winners(uint32_t gt, uint32_t eq, uint64_t eq_before, uint64_t need) {
-    const uint64_t left = eq_before < need ? need - eq_before : 0;
-    return (uint64_t)gt + (left < eq ? left : eq);
+
+// Whether a chunk's word does not hold its candidates inside the k-th key's bin.
+__device__ __forceinline__ bool chunk_again(uint32_t nb, uint64_t lows) {
+    return nb > kLowsMax && !(lows & kLowsSame);
 }
+
+// Candidates above and equal to the k-th key, whose low bits are `tau_low`,
+// from a chunk's counts and word.
+__device__ __forceinline__ void chunk_counts(uint32_t gt0, uint32_t nb, uint64_t lows, uint32_t tau_low,
+                                             uint32_t& gt, uint32_t& eq) {
+    gt = gt0;
+    eq = 0;
+    if (nb == 0) return;
+    if (lows & kLowsSame) {
+        const uint32_t x = (uint32_t)lows;
+        if (x > tau_low) gt += nb;
+        else if (x == tau_low) eq = nb;
+        return;
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < kLowsMax; ++q) {
+        const uint32_t x = (uint32_t)(lows >> (14u * q)) & 0x3FFFu;
+        gt += q < nb && x > tau_low ? 1u : 0u;
+        eq += q < nb && x == tau_low ? 1u : 0u;
+    }
+}
+
+// The same for a chunk whose candidates have to be read again, by a whole
+// wave, left in the chunk's counts and word: `gt` above, and `eq` with the
+// low bits tau_low.
+__device__ __forceinline__ void recount_chunk(const Ws& ws, uint32_t c, uint32_t w, uint32_t bin,
+                                              uint32_t tau_low, uint32_t& gt, uint32_t& eq) {
+    const uint32_t m = ws.t_ccount[c];
+    const uint2* cand = ws.t_cand + (size_t)c * kChunk;
+    const uint32_t low_mask = (1u << thr_shift(w)) - 1u;
+    gt = ws.t_gt[c];
+    eq = 0;
+    constexpr uint32_t kU = 4;
+    for (uint32_t i0 = 0; i0 < m; i0 += 64 * kU) {
+        uint32_t key[kU];
+#pragma unroll
+        for (uint32_t q = 0; q < kU; ++q) {
+            const uint32_t i = i0 + 64 * q + (uint32_t)lane_id();
+            key[q] = i < m ? cand[cand_at(c, m, i)].y & 0x7FFFFFFFu : 0u;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < kU; ++q) {
+            const bool inside = i0 + 64 * q + (uint32_t)lane_id() < m && cand_bin(key[q], w) == bin;
+            const uint32_t x = (key[q] - thr_key(w)) & low_mask;
+            gt += (uint32_t)__popcll(__ballot(inside && x > tau_low));
+            eq += (uint32_t)__popcll(__ballot(inside && x == tau_low));
+        }
+    }
+    if (lane_id() == 0) {
+        ws.t_gt[c] = gt;
+        ws.t_eq[c] = eq;
+        ws.t_off[c] = kLowsSame | tau_low;
+    }
+}
+
+// Winners of one chunk given the tau-equal candidates before it.
+__device__ __forceinline__ uint32_t chunk_winners(uint32_t gt, uint32_t eq, uint32_t eq_before, uint32_t need) {
+    const uint32_t left = eq_before < need ? need - eq_before : 0;
+    return gt + (left < eq ? left : eq);
+}
+
 }  // namespace
 
-__global__ __launch_bounds__(kBlock) void topk_cand_scan(const TDesc* __restrict__ d, Ws ws) {
-    __shared__ uint64_t sh[4];
+__global__ __launch_bounds__(kPlaceBlock) void topk_place(const TDesc* __restrict__ d, int copies, Ws ws) {
+    __shared__ uint32_t sh[4][kPlaceBlock / 64];
+    __shared__ uint32_t found[2];
     const int t = blockIdx.x;
     const TDesc td = d[t];
     if (td.k == 0 || td.nchunks == 0) return;
-    const uint64_t need = ws.t_krem[t];
-    const uint32_t per = (td.nchunks + kBlock - 1) / kBlock;
+    const uint32_t w = ws.t_thr[t], bin = ws.t_prefix[t], krem = ws.t_krem[t];
+    const uint32_t per = (td.nchunks + kPlaceBlock - 1) / kPlaceBlock;
     const uint32_t lo = threadIdx.x * per;
     const uint32_t hi = lo + per < td.nchunks ? lo + per : td.nchunks;
-    const uint32_t* eqp = ws.t_eq + td.chunk0;
-    const uint32_t* gtp = ws.t_gt + td.chunk0;
-    uint64_t tot;
-    if (per <= kScanRegs) {
-        uint32_t eq[kScanRegs], gt[kScanRegs];
+    uint32_t* eqp = ws.t_eq + td.chunk0;
+    uint32_t* gtp = ws.t_gt + td.chunk0;
+    uint64_t* offp = ws.t_off + td.chunk0;
+    uint32_t gt[kPlaceRegs], eq[kPlaceRegs];
+    uint64_t lows[kPlaceRegs];
+    const bool regs = per <= kPlaceRegs;
+    if (regs) {  // in flight during the search for tau
 #pragma unroll
-        for (uint32_t u = 0; u < kScanRegs; ++u) {
-            eq[u] = lo + u < hi ? eqp[lo + u] : 0u;
-            gt[u] = lo + u < hi ? gtp[lo + u] : 0u;
+        for (uint32_t u = 0; u < kPlaceRegs; ++u) {
+            const bool in = lo + u < hi;
+            gt[u] = in ? gtp[lo + u] : 0u;
+            eq[u] = in ? eqp[lo + u] : 0u;
+            lows[u] = in ? offp[lo + u] : 0u;
         }
-        uint64_t eq_run = 0;
+    }
+    // the krem-th largest of the low bits: thread i owns the i-th run of
+    // max(1, 2^s / 1024) bins from the top
+    const uint32_t bins = 1u << thr_shift(w), run = bins <= (uint32_t)kPlaceBlock ? 1u : bins / kPlaceBlock;
+    const bool owns = threadIdx.x * run < bins;
+    const uint32_t* gh = ws.t_hist + (size_t)t * copies * kBins0 + (owns ? bins - threadIdx.x * run : run);
+    uint32_t mine = 0;
+    for (uint32_t q = 1; owns && q <= run; ++q) mine += *(gh - q);
+    uint32_t above = wide_scan(mine, sh[0]);
+    if (owns && above < krem && krem <= above + mine) {
+        uint32_t q = 1, x = *(gh - 1);
+        while (krem > above + x) {
+            above += x;
+            x = *(gh - ++q);
+        }
+        found[0] = bins - threadIdx.x * run - q;
+        found[1] = above;
+    }
+    __syncthreads();
+    const uint32_t tau_low = found[0];
+    const uint32_t need = krem - found[1];
+    if (threadIdx.x == 0) {
+        ws.t_prefix[t] = thr_key(w) + (bin << thr_shift(w) | tau_low);
+        ws.t_krem[t] = need;
+    }
+    // chunks to read again (more candidates in the k-th key's bin than a word
+    // holds): the wave takes those of its lanes' runs one by one
+    bool any_again = !regs;
+    if (regs) {
 #pragma unroll
-        for (uint32_t u = 0; u < kScanRegs; ++u) eq_run += eq[u];
-        const uint64_t eqb0 = block_excl_scan_u64(eq_run, sh, tot);
-        uint64_t sel_run = 0, e = eqb0;
+        for (uint32_t q = 0; q < kPlaceRegs; ++q) any_again = any_again || chunk_again(eq[q], lows[q]);
+    }
+    for (uint32_t u = 0; __ballot(any_again) && u < per; ++u) {
+        const bool in = lo + u < hi;
+        uint32_t nb = 0;
+        uint64_t word = 0;
+        if (regs) {
 #pragma unroll
-        for (uint32_t u = 0; u < kScanRegs; ++u) {
+            for (uint32_t q = 0; q < kPlaceRegs; ++q)
+                if (q == u) {
+                    nb = eq[q];
+                    word = lows[q];
+                }
+        } else if (in) {
+            nb = eqp[lo + u];
+            word = offp[lo + u];
+        }
+        uint64_t again = __ballot(chunk_again(nb, word));
+        while (again) {
+            const int l = (int)__builtin_ctzll(again);
+            again &= again - 1;
+            uint32_t g, e;
+            recount_chunk(ws, td.chunk0 + (uint32_t)__builtin_amdgcn_readlane((int)(lo + u), l), w, bin, tau_low, g,
+                          e);
+            if (regs && lane_id() == l) {
+#pragma unroll
+                for (uint32_t q = 0; q < kPlaceRegs; ++q)
+                    if (q == u) {
+                        gt[q] = g;
+                        eq[q] = e;
+                        lows[q] = kLowsSame | tau_low;
+                    }
+            }
+        }
+    }
+    __syncthreads();  // counts and words written by other lanes
+    uint32_t eq_run = 0;
+    if (regs) {
+#pragma unroll
+        for (uint32_t u = 0; u < kPlaceRegs; ++u) {
+            if (__ballot(eq[u] != 0u)) {
+                chunk_counts(gt[u], eq[u], lows[u], tau_low, gt[u], eq[u]);
+                eq_run += eq[u];
+            }
+        }
+    } else {
+        for (uint32_t q = lo; q < hi; ++q) {
+            uint32_t g, e;
+            chunk_counts(gtp[q], eqp[q], offp[q], tau_low, g, e);
+            eq_run += e;
+        }
+    }
+    // tau-equal candidates before each run, then winners before each run
+    const uint32_t eqb0 = wide_scan(eq_run, sh[1]);
+    uint32_t sel_run = 0, e = eqb0;
+    if (regs) {
+#pragma unroll
+        for (uint32_t u = 0; u < kPlaceRegs; ++u) {
             sel_run += chunk_winners(gt[u], eq[u], e, need);
             e += eq[u];
         }
-        uint64_t pos = td.off + block_excl_scan_u64(sel_run, sh, tot);
-        e = eqb0;
+    } else {
+        for (uint32_t q = lo; q < hi; ++q) {
+            uint32_t g, x;
+            chunk_counts(gtp[q], eqp[q], offp[q], tau_low, g, x);
+            sel_run += chunk_winners(g, x, e, need);
+            e += x;
+        }
+    }
+    uint64_t pos = td.off + wide_scan(sel_run, sh[2]);
+    e = eqb0;
+    if (regs) {
 #pragma unroll
-        for (uint32_t u = 0; u < kScanRegs; ++u) {
+        for (uint32_t u = 0; u < kPlaceRegs; ++u) {
             if (lo + u < hi) {
-                const uint32_t c = td.chunk0 + lo + u;
-                ws.t_off[c] = pos;
-                ws.t_eqb[c] = (uint32_t)(e < 0xFFFFFFFFull ? e : 0xFFFFFFFFull);
+                offp[lo + u] = pos;
+                ws.t_eqb[td.chunk0 + lo + u] = e;
                 pos += chunk_winners(gt[u], eq[u], e, need);
                 e += eq[u];
             }
         }
-        return;
-    }
-    // tau-equal candidates before each run
-    uint64_t eq_run = 0;
-    for (uint32_t q0 = lo; q0 < hi; q0 += kScanBatch) {
-        uint32_t eq[kScanBatch];
-#pragma unroll
-        for (uint32_t u = 0; u < kScanBatch; ++u) eq[u] = q0 + u < hi ? eqp[q0 + u] : 0u;
-#pragma unroll
-        for (uint32_t u = 0; u < kScanBatch; ++u) eq_run += eq[u];
-    }
-    const uint64_t eqb0 = block_excl_scan_u64(eq_run, sh, tot);
-    // winners per chunk, and before each run
-    uint64_t sel_run = 0;
-    {
-        uint64_t e = eqb0;
-        for (uint32_t q0 = lo; q0 < hi; q0 += kScanBatch) {
-            uint32_t eq[kScanBatch], gt[kScanBatch];
-#pragma unroll
-            for (uint32_t u = 0; u < kScanBatch; ++u) {
-                eq[u] = q0 + u < hi ? eqp[q0 + u] : 0u;
-                gt[u] = q0 + u < hi ? gtp[q0 + u] : 0u;
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < kScanBatch; ++u) {
-                sel_run += chunk_winners(gt[u], eq[u], e, need);
-                e += eq[u];
-            }
-        }
-    }
-    uint64_t pos = td.off + block_excl_scan_u64(sel_run, sh, tot);
-    uint64_t eqb = eqb0;
-    for (uint32_t q0 = lo; q0 < hi; q0 += kScanBatch) {
-        uint32_t eq[kScanBatch], gt[kScanBatch];
-#pragma unroll
-        for (uint32_t u = 0; u < kScanBatch; ++u) {
-            eq[u] = q0 + u < hi ? eqp[q0 + u] : 0u;
-            gt[u] = q0 + u < hi ? gtp[q0 + u] : 0u;
-        }
-#pragma unroll
-        for (uint32_t u = 0; u < kScanBatch; ++u) {
-            if (q0 + u < hi) {
-                const uint32_t c = td.chunk0 + q0 + u;
-                ws.t_off[c] = pos;
-                ws.t_eqb[c] = (uint32_t)(eqb < 0xFFFFFFFFull ? eqb : 0xFFFFFFFFull);
-                pos += chunk_winners(gt[u], eq[u], eqb, need);
-                eqb += eq[u];
-            }
+    } else {
+        for (uint32_t q = lo; q < hi; ++q) {
+            uint32_t g, x;
+            chunk_counts(gtp[q], eqp[q], offp[q], tau_low, g, x);
+            offp[q] = pos;
+            ws.t_eqb[td.chunk0 + q] = e;
+            pos += chunk_winners(g, x, e, need);
+            e += x;
         }
     }
 }
 
 // Emit the winners of a chunk in index order and clear them in e_new (kDGC:
-// and in u), one wave per chunk; ranks come from ballots.
+// and in u) unless the stream pass has; candidates it cleared that lose get
+// their values back.  One wave per chunk; ranks come from ballots.
 template <bool kDGC>
 __global__ __launch_bounds__(kBlock) void topk_emit(const TDesc* __restrict__ d, int T, uint32_t C,
                                                     uint32_t* __restrict__ idx,
@@ -658,6 +1068,7 @@ __global__ __launch_bounds__(kBlock) void topk_emit(const TDesc* __restrict__ d,
         const uint64_t end = d[t].off + d[t].k;
         const uint32_t tau = ws.t_prefix[t];
         const uint64_t need = ws.t_krem[t];
+        const uint32_t zero = kDGC && m > kListMax ? kNoEarlyZero : ws.t_zero[t];
         const uint2* cand = ws.t_cand + (size_t)c * kChunk;
         uint64_t eq_seen = ws.t_eqb[c];
         uint64_t pos = ws.t_off[c];
@@ -666,7 +1077,7 @@ __global__ __launch_bounds__(kBlock) void topk_emit(const TDesc* __restrict__ d,
             uint2 e = make_uint2(0, 0);
             uint32_t key = 0;
             if (i < m) {
-                e = cand[i];
+                e = cand[cand_at(c, m, i)];
                 key = e.y & 0x7FFFFFFFu;
             }
             const bool is_eq = i < m && key == tau;
@@ -678,8 +1089,13 @@ __global__ __launch_bounds__(kBlock) void topk_emit(const TDesc* __restrict__ d,
             if (sel && at < end) {
                 idx[at] = e.x;
                 val[at] = u2f(e.y);
-                if (resid) gp(resid)[e.x] = 0.f;
-                if constexpr (kDGC) gp(vel_of(d[t]))[e.x] = 0.f;
+                if (key < zero) {
+                    if (resid) gp(resid)[e.x] = 0.f;
+                    if constexpr (kDGC) gp(vel_of(d[t]))[e.x] = 0.f;
+                }
+            } else if (i < m && key >= zero) {
+                if (resid) gp(resid)[e.x] = u2f(e.y);
+                if constexpr (kDGC) gp(vel_of(d[t]))[e.x] = *cand_vel(ws, c, i);
             }
             eq_seen += (uint64_t)__popcll(meq);
             pos += (uint64_t)__popcll(msel);
@@ -710,7 +1126,7 @@ __global__ __launch_bounds__(kBlock) void topk_emit(const TDesc* __restrict__ d,
 //             another and the pass needs no particular residency.
 // Histogram regions: digit 0 in `copies` copies (chunk c adds to copy
 // c % copies, which spreads the atomic additions to the busiest bins over
-// several addresses; readers add the copies) at t_hist[(r * T + t) * 2048],
+// several addresses; readers add the copies) at t_hist[(t * copies + r) * 2048],
 // then digit 1 at t_hist[copies * T * 2048 + t * 1024] and digit 2 at
 // t_hist[copies * T * 2048 + T * 1024 + t * 1024].
 // Look-back words (t_off, cleared by the histogram pass): bit 62 counts
@@ -839,8 +1255,8 @@ __global__ __launch_bounds__(kBlock) void topk_fast_compact(const TDesc* __restr
     load_stored_v(td, j, v, valid);  // in flight during the bin search
     for (int b = threadIdx.x; b < kBins12; b += kBlock) lh[b] = 0;
     uint32_t above;
-    const uint32_t b0 = block_hist_select(ws.t_hist + (size_t)t * kBins0, kBins0, td.k, sh, res_sh, &above, copies,
-                                          (size_t)T * kBins0);
+    const uint32_t b0 = block_hist_select(ws.t_hist + (size_t)t * copies * kBins0, kBins0, td.k, sh, res_sh, &above,
+                                          copies, kBins0);
     if (j == 0 && threadIdx.x == 0) {
         ws.t_thr[t] = b0 << 20;
         ws.t_fb[t] = td.k - above;  // entries still to select inside bin b
@@ -1042,8 +1458,7 @@ hipError_t launch_topk_t(int kind, double ratio, uint64_t seed, const TDesc* d, 
         uint32_t zb = (uint32_t)((hn / 4 + 255) / 256);
         if (zb > 4096) zb = 4096;
         hipLaunchKernelGGL(topk_zero_hist, dim3(zb), dim3(256), 0, s, ws.t_hist, hn, ws.t_any);
-        (void)launch_timed(kTimedTopkHist, topk_hist_pass<kDGC>, dim3(C), blk, 0, s, d, T, C, 1, 0, ws, ws.t_off,
-                           copies, f);
+        (void)launch_timed(kTimedTopkHist, topk_hist_pass<kDGC>, dim3(C), blk, 0, s, d, T, C, ws, ws.t_off, copies, f);
         hipLaunchKernelGGL(topk_fast_compact, dim3(C), blk, 0, s, d, T, C, copies, ws);
         hipLaunchKernelGGL(topk_fast_digit2, dim3(C), blk, 0, s, d, T, copies, ws);
         hipLaunchKernelGGL(topk_fast_emit<kDGC>, dim3((C + kBlock / 64 - 1) / (kBlock / 64)), blk, 0, s, d, T, C,
@@ -1051,48 +1466,31 @@ hipError_t launch_topk_t(int kind, double ratio, uint64_t seed, const TDesc* d, 
         return hipGetLastError();
     }
     const int R = topk_general_copies(T);
-    const uint64_t hn = (uint64_t)T * R * kBins0;
-    uint32_t zb = (uint32_t)((hn / 4 + 255) / 256);
-    if (zb > 4096) zb = 4096;
-    hipLaunchKernelGGL(topk_zero_hist, dim3(zb), dim3(256), 0, s, ws.t_hist, hn, ws.t_any);
     if (kind == 0) {  // exact
-        hipLaunchKernelGGL(topk_hist_pass<kDGC>, dim3(C), blk, 0, s, d, T, C, 1, 0, ws, (uint64_t*)nullptr, R, f);
-        hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindThrExact, 0, R, ws);
-        (void)launch_timed(kTimedTopkCompact, topk_compact<false, false>, dim3(C), blk, 0, s, d, T, C, 0, 0, R, ws,
-                           none);
-        hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindDigit0, 0, R, ws);
+        const uint64_t hn = (uint64_t)T * R * kBins0;
+        uint32_t zb = (uint32_t)((hn / 4 + 255) / 256);
+        if (zb > 4096) zb = 4096;
+        hipLaunchKernelGGL(topk_zero_hist, dim3(zb), dim3(256), 0, s, ws.t_hist, hn, ws.t_any);
+        hipLaunchKernelGGL(topk_hist_pass<kDGC>, dim3(C), blk, 0, s, d, T, C, ws, (uint64_t*)nullptr, R, f);
+        hipLaunchKernelGGL(topk_find_thr, dim3(T), blk, 0, s, d, R, ws);
+        (void)launch_timed(kTimedTopkCompact, topk_compact<false, false, false>, dim3(C), blk, 0, s, d, T, R, ws, none);
+        hipLaunchKernelGGL(topk_find_bin, dim3(T), blk, 0, s, d, R, ws);
     } else {  // sampled threshold, exact fallback per tensor
-        hipLaunchKernelGGL(topk_sample_hist<kDGC>, dim3((C + kSampleChunksPerBlock - 1) / kSampleChunksPerBlock),
-                           blk, 0, s, d, T, C, seed, R, ws, f);
-        hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindThrSample, 0, R, ws);
+        hipLaunchKernelGGL(topk_threshold<kDGC>, dim3(T), dim3(kThrBlock), 0, s, d, ratio, seed, R,
+                           topk_max_shift(R), ws, f);
         if (C > kNtChunks)
-            (void)launch_timed(kTimedTopkCompact, topk_compact<true, kDGC>, dim3(C), blk, 0, s, d, T, C, 1, 0, R, ws,
-                               f);
+            (void)launch_timed(kTimedTopkCompact, topk_compact<true, kDGC, true>, dim3(C), blk, 0, s, d, T, R, ws, f);
         else
-            (void)launch_timed(kTimedTopkCompact, topk_compact<false, kDGC>, dim3(C), blk, 0, s, d, T, C, 1, 0, R,
-                               ws, f);
-        hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindDigit0, 0, R, ws);
-        // fallback passes: small grids that walk the chunks, and return at
-        // once when no tensor fell back (the usual case); they re-read the
-        // stored v, so a DGC step needs nothing more here
-        const dim3 fb_grid(C < 1024u ? C : 1024u);
-        hipLaunchKernelGGL(topk_hist_pass<false>, fb_grid, blk, 0, s, d, T, C, 0, 1, ws, (uint64_t*)nullptr, R, none);
-        hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindThrExact, 1, R, ws);
-        hipLaunchKernelGGL((topk_compact<false, false>), fb_grid, blk, 0, s, d, T, C, 0, 1, R, ws, none);
-        hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindDigit0, 1, R, ws);
+            (void)launch_timed(kTimedTopkCompact, topk_compact<false, kDGC, true>, dim3(C), blk, 0, s, d, T, R, ws,
+                               f);
+        hipLaunchKernelGGL(topk_find_bin, dim3(T), blk, 0, s, d, R, ws);
+        hipLaunchKernelGGL(topk_fallback<kDGC>, dim3(C < 1024u ? C : 1024u), blk, 0, s, d, T, C, R, ws);
     }
-    uint32_t span = C / 1024u;
-    span = span < 1u ? 1u : (span > kCandSpanMax ? kCandSpanMax : span);
-    const dim3 hist_grid((C + span - 1) / span);
-    hipLaunchKernelGGL(topk_cand_hist, hist_grid, blk, 0, s, d, T, C, span, 1, R, ws);
-    hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindDigit1, 0, R, ws);
-    hipLaunchKernelGGL(topk_cand_hist, hist_grid, blk, 0, s, d, T, C, span, 2, R, ws);
-    hipLaunchKernelGGL(topk_find, dim3(T), blk, 0, s, d, T, ratio, (int)kFindDigit2, 0, R, ws);
     if (C >= kCountBatchFrom)
-        hipLaunchKernelGGL(topk_cand_count<4>, dim3((C + 15) / 16), blk, 0, s, d, T, C, ws);
+        hipLaunchKernelGGL(topk_cand_count<4>, dim3((C + 15) / 16), blk, 0, s, d, T, C, R, ws);
     else
-        hipLaunchKernelGGL(topk_cand_count<1>, dim3((C + 3) / 4), blk, 0, s, d, T, C, ws);
-    hipLaunchKernelGGL(topk_cand_scan, dim3(T), blk, 0, s, d, ws);
+        hipLaunchKernelGGL(topk_cand_count<1>, dim3((C + 3) / 4), blk, 0, s, d, T, C, R, ws);
+    hipLaunchKernelGGL(topk_place, dim3(T), dim3(kPlaceBlock), 0, s, d, R, ws);
     hipLaunchKernelGGL(topk_emit<kDGC>, dim3((C + kBlock / 64 - 1) / (kBlock / 64)), blk, 0, s, d, T, C, idx, val,
                        ws);
     return hipGetLastError();

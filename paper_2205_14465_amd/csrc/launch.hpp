@@ -32,16 +32,18 @@ struct Ws {
                             // (emptied before the kernel runs)
     // BC_TOPK, BC_TOPK_SAMPLED
     uint32_t* t_hist;       // [T * 2048] histograms         
-    uint32_t* t_thr;        // [T] candidate threshold (key)
-    uint32_t* t_prefix;     // [T] radix-select prefix (key)
+    uint32_t* t_thr;        // [T] candidate threshold (key; the general pipeline: with its bins' shift)
+    uint32_t* t_zero;       // [T] key from which the stream pass zeroes e_new at once (general pipeline;
+                            // after the histograms' copies, inside t_hist)
+    uint32_t* t_prefix;     // [T] radix-select prefix, then the k-th key
     uint32_t* t_krem;       // [T] entries still to select
     uint32_t* t_fb;         // [T] 1 = tensor needs the exact-histogram fallback
-    uint32_t* t_any;        // [1] nonzero when some tensor of the call needs it
+    uint32_t* t_any;        // [kAnyWords] nonzero when some tensor of the call needs it; the fallback's counters
     uint2* t_cand;          // [C * 4096] candidates (local index, value bits)
     uint32_t* t_ccount;     // [C] candidates per chunk
-    uint32_t* t_gt;         // [C] candidates above the threshold key
-    uint32_t* t_eq;         // [C] candidates equal to the threshold key
-    uint64_t* t_off;        // [C] payload position of a chunk's first winner
+    uint32_t* t_gt;         // [C] candidates above the k-th key's bin
+    uint32_t* t_eq;         // [C] candidates inside it
+    uint64_t* t_off;        // [C] their low bits, then the payload position of a chunk's first winner
     uint32_t* t_eqb;        // [C] equal-key candidates in earlier chunks
     // BC_RANDK
     uint32_t* r_keys;       // [T * 4] Feistel round keys
@@ -60,7 +62,7 @@ struct Ws {
 // size.  Regions a kind does not use have size 0.
 struct WsPlan {
     size_t flags, s_val, s_partial, s_info, s_tab, s_slot, q_max, q_slot;
-    size_t t_hist, t_thr, t_prefix, t_krem, t_fb, t_any, t_cand, t_ccount, t_gt, t_eq, t_off, t_eqb;
+    size_t t_hist, t_zero, t_thr, t_prefix, t_krem, t_fb, t_any, t_cand, t_ccount, t_gt, t_eq, t_off, t_eqb;
     size_t r_keys, r_tmp, r_ccount, r_coff, r_hist;
     size_t d_part, d_factor;
     size_t total;
@@ -114,10 +116,15 @@ bool take_kernel_timer(int k, hipEvent_t* start, hipEvent_t* stop);
 // a one-pass compress workgroup waits for the rest of its tensor's chunk
 // partials before it computes the missing ones itself.
 uint32_t onepass_wait_ticks();
+constexpr uint32_t kAnyWords = 6;
 // Copies of each top-k histogram in the general pipeline for a call of T
 // tensors: workgroups add into copy (their index mod copies), which spreads
 // the atomic additions to the busiest bins; readers add the copies.
-inline int topk_general_copies(int T) { return T <= 256 ? 8 : T <= 1024 ? 2 : 1; }  // at most 8
+constexpr int kGeneralCopiesMax = 4;
+inline int topk_general_copies(int T) { return T <= 256 ? kGeneralCopiesMax : 2; }
+// The copies' room later holds the histogram of the low s bits of the keys
+// in one candidate bin, so s is at most its logarithm (2048 words a copy).
+inline uint32_t topk_max_shift(int copies) { return copies == 4 ? 13u : 12u; }
 // A profiler range (roctx) around one C-ABI call: a push at construction,
 // the pop at scope exit; without a profiler attached both are plain calls.
 struct CallRange {

@@ -169,6 +169,62 @@ def test_dgc_sampled_fallback_mixed(ratio):
                 assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), (step, t)
 
 
+def _awkward(case, n, rng):
+    """Values on which the general pipeline's thresholds, bins and early
+    zeros go wrong in one way each."""
+    if case == "heavy_tail":    # the k-th key lies past the bins' range, or the sample misleads
+        return np.exp(rng.standard_normal(n) * 9.0).clip(1e-30, 1e30)
+    if case == "tight":         # many different keys in one bin of a chunk
+        return 1.0 + rng.random(n) * 2.0 ** -9
+    if case == "equal":
+        return np.full(n, 0.375)
+    if case == "zeros":         # fewer non-zero elements than k
+        return rng.standard_normal(n) * (rng.random(n) < 0.004)
+    if case == "blocks":        # the large values in blocks that the sample meets or misses
+        x = rng.standard_normal(n) * 0.01
+        at = rng.integers(0, max(1, n // 64), size=max(1, n // 64 * 13 // 1000)) if n >= 64 else []
+        for b in at:
+            x[64 * b:64 * b + 64] = 3.0 + rng.standard_normal(64) * 0.2
+        return x
+    raise ValueError(case)
+
+
+@pytest.mark.parametrize("dgc", [False, True])
+@pytest.mark.parametrize("case", ["heavy_tail", "tight", "equal", "zeros", "blocks"])
+def test_topk_general_awkward_values(case, dgc):
+    """General pipeline, sampled kind, against the oracle bit for bit, at
+    sizes around the sampling limit and with ragged ends: the exact fallback,
+    chunks whose k-th bin holds more candidates than fit a word, early zeros
+    that have to be taken back (e and, under DGC, u)."""
+    import torch
+    from paper_2205_14465_amd import binding as B
+    ns = [16383, 16384, 16385, 250003, 70001, 4, 3, 1]
+    ratio, m = 0.01, 0.9
+    for seed in range(8 if case == "blocks" else 2):
+        rng = np.random.default_rng(100 + seed)
+        grads = [_awkward(case, n, rng).astype(np.float32) for n in ns]
+        e = [np.zeros(n, np.float32) for n in ns]
+        u = [np.zeros(n, np.float32) for n in ns]
+        dg, de, du = [torch_dev(x) for x in grads], [torch_dev(x) for x in e], [torch_dev(x) for x in u]
+        out = B.alloc_payload("topk_sampled", ratio, ns)
+        ws = B.alloc_workspace("topk_sampled", ratio, ns, 1)
+        with topk_path("general"):
+            if dgc:
+                B.bytecomp_compress_dgc("topk_sampled", ratio, seed, m, dg, de, du, out, ws)
+                want, e, u = O.compress_dgc_set("topk_sampled", ratio, seed, m, grads, e, u)
+            else:
+                B.bytecomp_compress("topk_sampled", ratio, seed, dg, de, out, ws)
+                want, e = O.compress_set("topk_sampled", ratio, seed, grads, e)
+        torch.cuda.synchronize()
+        total = int(want["off"][-1])
+        assert np.array_equal(out["idx"].cpu().numpy().view(np.uint32)[:total], want["idx"]), seed
+        assert np.array_equal(bits(out["val"].cpu().numpy()[:total]), bits(want["val"])), seed
+        for t in range(len(ns)):
+            assert np.array_equal(bits(de[t].cpu().numpy()), bits(e[t])), (seed, t)
+            if dgc:
+                assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), (seed, t)
+
+
 @pytest.mark.timeout(600)
 def test_dgc_randk_many_chunks():
     """Random-k DGC on a call of more than 32768 chunks (40000 one-chunk
