@@ -145,13 +145,73 @@ __device__ __forceinline__ int wave_id() {
 }
 
 // ----------------------------------------------------------- chunk loading
-// A chunk that lies wholly inside its tensor (every chunk but a tensor's
-// last, in general) is read by straight-line code that issues all of a
+// Every chunk is read by the same straight-line code, which issues all of a
 // thread's vector loads before it uses any of them, so that they are in
-// flight together; the per-element path serves the tensor's last chunk.
-// The test is uniform over the workgroup (one chunk, one tensor).
+// flight together.  In a tensor's last chunk, groups of four that reach past
+// the tensor's end read its last four elements instead (an address that may
+// be aligned to an element only, which the hardware's vector loads take), and
+// mend_tail puts what exists into place.  Only tensors of fewer than four
+// elements are read one by one.  (A last chunk read element by element cost
+// a list of 4096 tensors of 768 to 65536 elements, a quarter of whose
+// chunks are last ones, 10 us of a 260 us sign step.)  The tests are
+// uniform over the workgroup (one chunk, one tensor).
 __device__ __forceinline__ bool whole_chunk(const TDesc& td, uint32_t j) {
     return (uint64_t)j * kChunk + kChunk <= td.n;
+}
+
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
+// Four consecutive elements from element i on, any i.
+template <bool kNT = false>
+__device__ __forceinline__ f32x4 ldg4f_any(const float* p) {
+    if constexpr (kNT) return __builtin_nontemporal_load((const BC_GLOBAL f32x4_any*)p);
+    else return *(const BC_GLOBAL f32x4_any*)p;
+}
+template <bool kNT = false>
+__device__ __forceinline__ u32x2 ldg4h_any(const uint16_t* p) {
+    if constexpr (kNT) return __builtin_nontemporal_load((const BC_GLOBAL u32x2_any*)p);
+    else return *(const BC_GLOBAL u32x2_any*)p;
+}
+
+// First element that a thread's load of round r covers: its own group's, or
+// the fourth from the tensor's end (n >= 4).
+__device__ __forceinline__ uint32_t load_at(uint32_t n, uint32_t j, int r) {
+    const uint32_t e = j * (uint32_t)kChunk + 1024u * r + 4u * threadIdx.x;
+    return e < n - 4u ? e : n - 4u;
+}
+
+// Which of a thread's elements exist in chunk j of a tensor of n elements.
+__device__ __forceinline__ uint32_t valid_of(uint32_t n, uint32_t j) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t e = j * (uint32_t)kChunk + 1024u * r + 4u * threadIdx.x;
+        const uint32_t left = e < n ? n - e : 0u;
+        m |= (left >= 4u ? 0xFu : (1u << left) - 1u) << (4 * r);
+    }
+    return m;
+}
+
+// v formed from a last chunk's loads: the group that straddles the tensor's
+// end holds the last four elements and keeps those from its first on; the
+// elements past the end become +0.0.
+__device__ __forceinline__ void mend_tail(uint32_t n, uint32_t valid, float (&v)[kEpt]) {
+    // elements of the straddling group (its first one is loaded last - rest);
+    // a tensor of fewer than four elements is in place already
+    const uint32_t rest = n >= 4u ? n & 3u : 0u;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) {
+        const uint32_t m = (valid >> (4 * r)) & 0xFu;
+        const float x0 = v[4 * r], x1 = v[4 * r + 1], x2 = v[4 * r + 2], x3 = v[4 * r + 3];
+        const bool cut = m != 0xFu;
+        const float y0 = !cut || rest == 0u ? x0 : rest == 1u ? x3 : rest == 2u ? x2 : x1;
+        const float y1 = !cut || rest == 0u ? x1 : rest == 2u ? x3 : x2;
+        const float y2 = !cut || rest == 0u ? x2 : x3;
+        v[4 * r] = m & 1u ? y0 : 0.f;
+        v[4 * r + 1] = m & 2u ? y1 : 0.f;
+        v[4 * r + 2] = m & 4u ? y2 : 0.f;
+        v[4 * r + 3] = m & 8u ? x3 : 0.f;
+    }
 }
 
 // Widened gradient element q (0..3) of a thread's round: fp32 bits, or the
@@ -168,22 +228,20 @@ __device__ __forceinline__ float g_elem(const f32x4& gf, const u32x2& gh, int q)
 // invalid through `valid` (bit 4*r + q).
 template <int DT, bool kNT = false>
 __device__ __forceinline__ void load_chunk(const TDesc& td, uint32_t j, bool use_resid,
-                                           float v[kEpt], uint32_t& valid) {
-    const uint32_t base = j * (uint32_t)kChunk;
+                                           float (&v)[kEpt], uint32_t& valid) {
     const uint32_t n = td.n;
-    if (whole_chunk(td, j)) {
+    if (n >= 4u) {
         f32x4 gf[kRounds];
         u32x2 gh[kRounds];
-        const uint32_t e0 = base + 4u * threadIdx.x;
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            if constexpr (DT == 0) gf[r] = ldg4f_s<kNT>((const float*)td.grad + e0 + 1024u * r);
-            else gh[r] = ldg2u_s<kNT>((const uint16_t*)td.grad + e0 + 1024u * r);
+            if constexpr (DT == 0) gf[r] = ldg4f_any<kNT>((const float*)td.grad + load_at(n, j, r));
+            else gh[r] = ldg4h_any<kNT>((const uint16_t*)td.grad + load_at(n, j, r));
         }
         if (use_resid) {
             f32x4 ev[kRounds];
 #pragma unroll
-            for (int r = 0; r < kRounds; ++r) ev[r] = ldg4f_s<kNT>(td.resid + e0 + 1024u * r);
+            for (int r = 0; r < kRounds; ++r) ev[r] = ldg4f_any<kNT>(td.resid + load_at(n, j, r));
 #pragma unroll
             for (int r = 0; r < kRounds; ++r)
 #pragma unroll
@@ -194,50 +252,29 @@ __device__ __forceinline__ void load_chunk(const TDesc& td, uint32_t j, bool use
 #pragma unroll
                 for (int q = 0; q < 4; ++q) v[4 * r + q] = g_elem<DT>(gf[r], gh[r], q);
         }
-        valid = 0xFFFFu;
-        return;
-    }
-    valid = 0;
+    } else {
 #pragma unroll
-    for (int r = 0; r < kRounds; ++r) {
-        const uint32_t e0 = base + 1024u * r + 4u * threadIdx.x;
-        float g4[4] = {0.f, 0.f, 0.f, 0.f};
-        float e4[4] = {0.f, 0.f, 0.f, 0.f};
-        if (e0 + 3 < n) {
-            if (DT == 0) {
-                const f32x4 x = ldg4f_s<kNT>((const float*)td.grad + e0);
-                g4[0] = x.x; g4[1] = x.y; g4[2] = x.z; g4[3] = x.w;
-            } else {
-                const u32x2 h = ldg2u_s<kNT>((const uint16_t*)td.grad + e0);
-                g4[0] = h2f(h.x & 0xFFFFu);
-                g4[1] = h2f(h.x >> 16);
-                g4[2] = h2f(h.y & 0xFFFFu);
-                g4[3] = h2f(h.y >> 16);
-            }
-            if (use_resid) {
-                const f32x4 y = ldg4f_s<kNT>(td.resid + e0);
-                e4[0] = y.x; e4[1] = y.y; e4[2] = y.z; e4[3] = y.w;
-            }
-            valid |= 0xFu << (4 * r);
-        } else {
+        for (int i = 0; i < kEpt; ++i) v[i] = 0.f;
+        if (threadIdx.x == 0) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (e0 + q < n) {
-                    if (DT == 0) g4[q] = gp((const float*)td.grad)[e0 + q];
-                    else g4[q] = h2f(gp((const uint16_t*)td.grad)[e0 + q]);
-                    if (use_resid) e4[q] = gp(td.resid)[e0 + q];
-                    valid |= 1u << (4 * r + q);
-                }
+            for (uint32_t q = 0; q < 3; ++q) {
+                if (q >= n) continue;
+                if (DT == 0) v[q] = gp((const float*)td.grad)[q];
+                else v[q] = h2f(gp((const uint16_t*)td.grad)[q]);
+                if (use_resid) v[q] = v[q] + gp(td.resid)[q];
             }
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[4 * r + q] = use_resid ? g4[q] + e4[q] : g4[q];
+    }
+    valid = 0xFFFFu;
+    if (!whole_chunk(td, j)) {
+        valid = valid_of(n, j);
+        mend_tail(n, valid, v);
     }
 }
 
 // Runtime dtype dispatch (uniform per workgroup: a chunk has one tensor).
 template <bool kNT = false>
-__device__ __forceinline__ void load_v(const TDesc& td, uint32_t j, bool use_resid, float v[kEpt],
+__device__ __forceinline__ void load_v(const TDesc& td, uint32_t j, bool use_resid, float (&v)[kEpt],
                                        uint32_t& valid) {
     if (td.dtype == 0) load_chunk<0, kNT>(td, j, use_resid, v, valid);
     else load_chunk<1, kNT>(td, j, use_resid, v, valid);
@@ -265,17 +302,17 @@ __device__ __forceinline__ void load_raw(const TDesc& td, uint32_t j, bool use_r
         if (td.dtype == 0) load_raw<0>(td, j, use_resid, r);
         else load_raw<1>(td, j, use_resid, r);
     } else {
-        const uint32_t base = j * (uint32_t)kChunk;
         const uint32_t n = td.n;
-        if (whole_chunk(td, j)) {
-            const uint32_t e0 = base + 4u * threadIdx.x;
+        r.valid = whole_chunk(td, j) ? 0xFFFFu : valid_of(n, j);
+        if (n >= 4u) {
 #pragma unroll
             for (int rr = 0; rr < kRounds; ++rr) {
                 if constexpr (kDT == 0) {
-                    const u32x4 x = ldg4u((const float*)td.grad + e0 + 1024u * rr);
-                    r.g[4 * rr] = x.x; r.g[4 * rr + 1] = x.y; r.g[4 * rr + 2] = x.z; r.g[4 * rr + 3] = x.w;
+                    const f32x4 x = ldg4f_any((const float*)td.grad + load_at(n, j, rr));
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) r.g[4 * rr + q] = f2u(x[q]);
                 } else {
-                    const u32x2 h = ldg2u((const uint16_t*)td.grad + e0 + 1024u * rr);
+                    const u32x2 h = ldg4h_any((const uint16_t*)td.grad + load_at(n, j, rr));
                     r.g[4 * rr] = h.x;
                     r.g[4 * rr + 1] = h.y;
                 }
@@ -283,84 +320,52 @@ __device__ __forceinline__ void load_raw(const TDesc& td, uint32_t j, bool use_r
             if (use_resid) {
 #pragma unroll
                 for (int rr = 0; rr < kRounds; ++rr) {
-                    const f32x4 y = ldg4f(td.resid + e0 + 1024u * rr);
-                    r.e[4 * rr] = y.x; r.e[4 * rr + 1] = y.y; r.e[4 * rr + 2] = y.z; r.e[4 * rr + 3] = y.w;
+                    const f32x4 y = ldg4f_any(td.resid + load_at(n, j, rr));
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) r.e[4 * rr + q] = y[q];
                 }
             }
-            r.valid = 0xFFFFu;
             return;
         }
-        r.valid = 0;
+        if (threadIdx.x != 0) return;  // the others have no elements
 #pragma unroll
-        for (int rr = 0; rr < kRounds; ++rr) {
-            const uint32_t e0 = base + 1024u * rr + 4u * threadIdx.x;
-            if constexpr (kDT == 1) {
-                r.g[4 * rr] = 0u;
-                r.g[4 * rr + 1] = 0u;
+        for (uint32_t q = 0; q < 3; ++q) {
+            const uint32_t i = q < n ? q : 0u;
+            if constexpr (kDT == 0) {
+                r.g[q] = gp((const uint32_t*)td.grad)[i];
+            } else {
+                const uint32_t hb = (uint32_t)gp((const uint16_t*)td.grad)[i];
+                if (q == 1) r.g[0] |= hb << 16;
+                else r.g[q >> 1] = hb;
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bool ok = e0 + q < n;
-                if constexpr (kDT == 0) {
-                    r.g[4 * rr + q] = ok ? gp((const uint32_t*)td.grad)[e0 + q] : 0u;
-                } else {
-                    const uint32_t hb = ok ? (uint32_t)gp((const uint16_t*)td.grad)[e0 + q] : 0u;
-                    r.g[4 * rr + (q >> 1)] |= hb << (16 * (q & 1));
-                }
-                if (use_resid) r.e[4 * rr + q] = ok ? gp(td.resid)[e0 + q] : 0.f;
-                r.valid |= (ok ? 1u : 0u) << (4 * rr + q);
-            }
+            if (use_resid) r.e[q] = gp(td.resid)[i];
         }
     }
 }
 
 // v = widen(g) + e from a RawChunk (e = 0 without residual), exactly as
-// load_v forms it; elements past the tensor's end read as +0.0.
+// load_v forms it (whole: whole_chunk of it); elements past the tensor's end
+// read as +0.0.
 template <int kDT>
-__device__ __forceinline__ void raw_to_v(const TDesc& td, bool use_resid, const RawChunk& r, float v[kEpt]) {
+__device__ __forceinline__ void raw_to_v(const TDesc& td, bool whole, bool use_resid, const RawChunk& r,
+                                         float (&v)[kEpt]) {
     const bool f16 = kDT == 1 || (kDT == 2 && td.dtype != 0);
 #pragma unroll
     for (int i = 0; i < kEpt; ++i) {
-        float g = f16 ? h2f((r.g[(i & ~3) + ((i >> 1) & 1)] >> (16 * (i & 1))) & 0xFFFFu) : u2f(r.g[i]);
-        g = ((r.valid >> i) & 1u) ? g : 0.f;
+        const float g = f16 ? h2f((r.g[(i & ~3) + ((i >> 1) & 1)] >> (16 * (i & 1))) & 0xFFFFu) : u2f(r.g[i]);
         v[i] = use_resid ? g + r.e[i] : g;
     }
+    if (!whole) mend_tail(td.n, r.valid, v);
 }
 
 // Load v that an earlier pass already stored (the residual buffer holds v),
 // or recompute it from the gradient when error feedback is off.
-__device__ __forceinline__ void load_stored_v(const TDesc& td, uint32_t j, float v[kEpt],
+__device__ __forceinline__ void load_stored_v(const TDesc& td, uint32_t j, float (&v)[kEpt],
                                               uint32_t& valid) {
     if (td.resid) {
-        const uint32_t base = j * (uint32_t)kChunk;
-        if (whole_chunk(td, j)) {
-            f32x4 y[kRounds];
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r) y[r] = ldg4f(td.resid + base + 1024u * r + 4u * threadIdx.x);
-#pragma unroll
-            for (int r = 0; r < kRounds; ++r)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[4 * r + q] = y[r][q];
-            valid = 0xFFFFu;
-            return;
-        }
-        valid = 0;
-#pragma unroll
-        for (int r = 0; r < kRounds; ++r) {
-            const uint32_t e0 = base + 1024u * r + 4u * threadIdx.x;
-            if (e0 + 3 < td.n) {
-                const f32x4 y = ldg4f(td.resid + e0);
-                v[4 * r] = y.x; v[4 * r + 1] = y.y; v[4 * r + 2] = y.z; v[4 * r + 3] = y.w;
-                valid |= 0xFu << (4 * r);
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    bool ok = e0 + q < td.n;
-                    v[4 * r + q] = ok ? gp(td.resid)[e0 + q] : 0.f;
-                    valid |= (ok ? 1u : 0u) << (4 * r + q);
-                }
-            }
-        }
+        TDesc te = td;  // v as an fp32 tensor of its own
+        te.grad = td.resid;
+        load_chunk<0>(te, j, false, v, valid);
     } else if (td.dtype == 0) {
         load_chunk<0>(td, j, false, v, valid);
     } else {

@@ -381,7 +381,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         if (have) {
             const int t = tensor_of_chunk(d, T, c);
             j = c - td.chunk0;
-            raw_to_v<kDT>(td, td.resid != nullptr, raw, v);
+            raw_to_v<kDT>(td, whole_chunk(td, j), td.resid != nullptr, raw, v);
             uint32_t mk = 0;
 #pragma unroll
             for (int i = 0; i < kEpt; ++i) {

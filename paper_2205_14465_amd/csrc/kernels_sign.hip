@@ -250,7 +250,7 @@ __device__ __forceinline__ float onepass_scale(const TDesc& td, uint64_t* slot, 
 }  // namespace
 
 template <int kDT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void sign_onepass(const TDesc* __restrict__ d, int T, uint32_t C,
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1 ? 5 : 4))) void sign_onepass(const TDesc* __restrict__ d, int T, uint32_t C,
                                                        uint32_t* __restrict__ bits, float* __restrict__ scale_out,
                                                        Ws ws, uint32_t wait_ticks) {
     __shared__ double sh[4];
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
         if (have) {
             const int t = tensor_of_chunk(d, T, c);
             j = c - td.chunk0;
-            raw_to_v<kDT>(td, td.resid != nullptr, raw, v);
+            raw_to_v<kDT>(td, whole_chunk(td, j), td.resid != nullptr, raw, v);
             store_sign_words(v, bits + td.off + (uint64_t)j * kChunkWords, chunk_words(td, j));
             const double p = block_sum_f64(thread_abs_sum(v), sh);
             if (td.nchunks == 1) {

@@ -646,7 +646,7 @@ __device__ __forceinline__ void compact_chunk(const TDesc& td, int t, uint32_t c
 }
 
 template <bool kNT, bool kDGC, bool kStream>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void topk_compact(
+__global__ __launch_bounds__(kBlock) void topk_compact(
     const TDesc* __restrict__ d, int T, int copies, Ws ws, DgcFuse f) {
     __shared__ CompactLds l;
     __shared__ float list_u[kDGC && kStream ? kListMax : 1];
