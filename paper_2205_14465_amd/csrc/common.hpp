@@ -397,6 +397,27 @@ __device__ __forceinline__ void store_chunk(float* dst, uint32_t n, uint32_t j, 
     }
 }
 
+// A unit of 4096 results, of which lane l of the workgroup holds elements
+// 16 l .. 16 l + 15, on its way to coalesced stores through LDS: written so,
+// every store instruction of the workgroup covers 4 KiB of the output
+// without gaps (lane-wise 64-byte pieces left each instruction a quarter of
+// every line).  The four 16-byte pieces of a lane are rotated by l / 4, so
+// that neither side meets a bank conflict.
+__device__ __forceinline__ uint32_t staged_at(uint32_t piece) {
+    const uint32_t l = piece >> 2;
+    return 16u * l + 4u * ((piece + (l >> 2)) & 3u);
+}
+__device__ __forceinline__ void stage_results(float* lds, const float (&res)[16]) {
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c)
+        *reinterpret_cast<f32x4*>(lds + staged_at(4u * threadIdx.x + c)) =
+            f32x4{res[4 * c], res[4 * c + 1], res[4 * c + 2], res[4 * c + 3]};
+}
+// After a barrier: piece k of this lane, elements 1024 k + 4 l .. + 3.
+__device__ __forceinline__ f32x4 staged_piece(const float* lds, uint32_t k) {
+    return *reinterpret_cast<const f32x4*>(lds + staged_at(256u * k + threadIdx.x));
+}
+
 // --------------------------------------------------------- block reductions
 // Sum of a double over the 256 threads in a fixed tree (deterministic for a
 // given block shape); every thread receives the total.

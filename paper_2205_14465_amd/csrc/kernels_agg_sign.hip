@@ -160,18 +160,6 @@ __device__ __forceinline__ void lookup_step_half(double (&S)[8], const uint32_t*
     }
 }
 
-__device__ __forceinline__ void store16(const ADesc& ad, uint32_t e0, const float (&res)[16]) {
-    float* out = ad.out + e0;
-    if (e0 + 16u <= ad.n) {
-#pragma unroll
-        for (int q = 0; q < 16; q += 4) stg4f(out + q, f32x4{res[q], res[q + 1], res[q + 2], res[q + 3]});
-    } else {
-#pragma unroll
-        for (int q = 0; q < 16; ++q)
-            if (e0 + q < ad.n) gp(out)[q] = res[q];
-    }
-}
-
 }  // namespace
 
 // Sign aggregate.  A unit is 128 consecutive payload words (4096 output
@@ -311,23 +299,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
             for (int q = 0; q < 8; ++q) res[8 * half + q] = alpha * (float)S[q];
         }
     }
-    // Lane l holds unit elements 16 l .. 16 l + 15.  Through LDS (element e
-    // of the unit at lds[e]), store k of the workgroup writes elements
-    // 1024 k + 4 l' .. +3 for lane l': every store instruction covers 1 KiB
-    // of the output.  ebase is a multiple of 32, so whole groups of four
-    // are inside or outside [0, n) at the tensor's start.
+    // ebase is a multiple of 32, so whole groups of four are inside or
+    // outside [0, n) at the tensor's start.
     __syncthreads();  // every wave is past its lookups
-#pragma unroll
-    for (int c = 0; c < 4; ++c)
-        *reinterpret_cast<f32x4*>(lds + 16 * threadIdx.x + 4 * c) =
-            f32x4{res[4 * c], res[4 * c + 1], res[4 * c + 2], res[4 * c + 3]};
+    stage_results(lds, res);
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t e = 1024u * k + 4u * threadIdx.x;  // element of the unit
-        const int64_t g = ebase + e;                       // element of the tensor
+    for (uint32_t k = 0; k < 4; ++k) {
+        const int64_t g = ebase + 1024u * k + 4u * threadIdx.x;  // element of the tensor
         if (g < 0) continue;
-        const f32x4 v = *reinterpret_cast<const f32x4*>(lds + e);
+        const f32x4 v = staged_piece(lds, k);
         if (g + 4 <= (int64_t)ad.n) {
             stg4f(ad.out + g, v);
         } else {

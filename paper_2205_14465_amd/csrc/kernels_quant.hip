@@ -596,17 +596,13 @@ __device__ __forceinline__ void tern_indices(const uint32_t (&x)[4], uint32_t (&
 // tensor's tables into LDS, loads the words of all (at most 16 kTS) workers
 // at once, and adds one table entry per element and group of four workers
 // in int32.  Other tensors take the wide exact path.
-template <int kBits, int kTS>
+template <int kBits>
 __global__ __launch_bounds__(kBlock) void aggregate_quant(const ADesc* __restrict__ a, int T, uint32_t U,
-                                                          const uint64_t* __restrict__ wp, int W, float alpha,
-                                                          const uint32_t* __restrict__ info,
-                                                          const int32_t* __restrict__ tabs) {
+                                                          const uint64_t* __restrict__ wp, int W, float alpha) {
     constexpr int kWords = kBits / 2;
     constexpr int kGroup = 8;  // workers whose words are in flight together
     using Q = Quant<kBits>;
     __shared__ float unit_sh[1024];
-    __shared__ __attribute__((aligned(16))) int32_t tab_sh[kBits == 2 ? 256 * 4 * kTS : 4];
-    static_assert(kBits != 2 || sizeof(tab_sh) >= kWideScratchBytes, "wide-path scratch");
     const uint32_t u = blockIdx.x;
     const int t = unit_owner(wp, W, u);
     const ADesc ad = a[t];
@@ -642,69 +638,18 @@ __global__ __launch_bounds__(kBlock) void aggregate_quant(const ADesc* __restric
     float acc[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] = 0.f;
-    if constexpr (kBits == 2) {
-        const uint32_t inf = info[t];
-        if ((inf & 255u) != 1u) {
-            // scales the int32 tables cannot hold exactly (or more than 64
-            // workers): the wide exact path writes the unit's outputs itself
-            aggregate_unit_exact_wide<1>(ad, (int64_t)(u - ad.unit0) * kSignAggUnit, wp, W, alpha, unit_sh,
-                                         reinterpret_cast<unsigned char*>(tab_sh));
-            return;
-        }
-        {
-            const int G4 = (W + 3) / 4;  // <= 4 kTS
-            const int32_t* tt = tabs + (size_t)t * kTernTab;
-            uint32_t wv[16 * kTS];
-#pragma unroll
-            for (int k = 0; k < 16 * kTS; ++k) {
-                uint32_t wd[1];
-                load_words(w_a(wp, k < W ? k : W - 1) + ad.off, wd);
-                wv[k] = wd[0];
-            }
-            for (int x = 4 * (int)threadIdx.x; x < 256 * G4; x += 4 * kBlock)
-                *reinterpret_cast<u32x4*>(tab_sh + x) = ldg4u(tt + x);
-            __syncthreads();
-            int32_t S[16];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) S[q] = 0;
-#pragma unroll
-            for (int g = 0; g < 4 * kTS; ++g) {
-                if (g < G4) {
-                    const uint32_t xw[4] = {wv[4 * g], wv[4 * g + 1], wv[4 * g + 2], wv[4 * g + 3]};
-                    uint32_t y[4];
-                    tern_indices(xw, y);
-                    const int32_t* tg = tab_sh + 256 * g;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) S[4 * j + i] += tg[(y[j] >> (8 * i)) & 255u];
-                }
-            }
-            // exact: |S| < 2^31 and the unit is a power of two
-            const double unit = __builtin_ldexp(1.0, (int)((inf >> 8) & 255u) - 150);
-#pragma unroll
-            for (int q = 0; q < 16; ++q) acc[q] = (float)((double)S[q] * unit);
-        }
-    }
     auto add_worker = [&](const uint32_t (&wd)[kWords], float un) {
-        const uint32_t ub = f2u(un);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             constexpr int kPer = 32 / kBits;
             const uint32_t word = wd[q / kPer];
             const int pos = (q % kPer) * kBits;  // first bit of the code
-            float mag;
-            if constexpr (kBits == 2) {
-                mag = u2f(ub & (uint32_t)__builtin_amdgcn_sbfe((int)word, pos, 1));
-            } else {
-                mag = (float)__builtin_amdgcn_ubfe(word, pos, kBits - 1) * un;
-            }
+            const float mag = (float)__builtin_amdgcn_ubfe(word, pos, kBits - 1) * un;
             const uint32_t sgn = word << (31 - (pos + kBits - 1));  // the code's sign bit at bit 31
             acc[q] += u2f((sgn & 0x80000000u) ^ f2u(mag));
         }
     };
     int w0 = 0;
-    if constexpr (kBits == 2) w0 = W;  // summed on the table path
     for (; w0 + kGroup <= W; w0 += kGroup) {
         uint32_t wd[kGroup][kWords];
 #pragma unroll
@@ -726,6 +671,92 @@ __global__ __launch_bounds__(kBlock) void aggregate_quant(const ADesc* __restric
 #pragma unroll
         for (int q = 0; q < 16; ++q)
             if (e_first + q < ad.n) gp(out)[q] = alpha * acc[q];
+    }
+}
+
+namespace {
+// Outputs e .. e+3 of a tensor, as far as they exist.
+__device__ __forceinline__ void store_group(const ADesc& ad, uint32_t e, f32x4 v) {
+    if ((uint64_t)e + 4u <= ad.n) {
+        stg4f(ad.out + e, v);
+    } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if ((uint64_t)e + q < ad.n) gp(ad.out)[e + q] = v[q];
+    }
+}
+}  // namespace
+
+// TernGrad aggregate: a workgroup sums 4096 elements, 16 per lane, one word
+// of every worker.  Lanes past the tensor's end read its last word and their
+// results are not stored, so that every unit runs the same straight code, all
+// W words in flight (a separate path for a tensor's last unit kept the loads
+// behind a branch: 156 us for 25.6 M elements and W = 64, 120 us now).
+template <int kTS>
+__global__ __launch_bounds__(kBlock) void aggregate_tern(const ADesc* __restrict__ a, int T, uint32_t U,
+                                                         const uint64_t* __restrict__ wp, int W, float alpha,
+                                                         const uint32_t* __restrict__ info,
+                                                         const int32_t* __restrict__ tabs) {
+    __shared__ float unit_sh[1024];
+    // the tables, then the unit's results
+    __shared__ __attribute__((aligned(16))) int32_t tab_sh[4096];
+    static_assert(256 * 4 * kTS <= 4096 && sizeof(tab_sh) >= kWideScratchBytes, "LDS size");
+    const uint32_t u = blockIdx.x;
+    const int t = unit_owner(wp, W, u);
+    const ADesc ad = a[t];
+    const uint32_t e_unit = (u - ad.unit0) * kSignAggUnit;  // element of the tensor
+    const uint32_t inf = info[t];
+    if ((inf & 255u) != 1u) {
+        // scales the int32 tables cannot hold exactly (or more than 64
+        // workers): the wide exact path writes the unit's outputs itself
+        for (int w = threadIdx.x; w < W; w += kBlock) unit_sh[w] = gp(w_b(wp, W, w))[t];
+        __syncthreads();
+        aggregate_unit_exact_wide<1>(ad, (int64_t)e_unit, wp, W, alpha, unit_sh,
+                                     reinterpret_cast<unsigned char*>(tab_sh));
+        return;
+    }
+    // lane l: the elements 16 l .. 16 l + 15 of the unit, one word of
+    // every worker (past the tensor's end its last word: those results
+    // are not stored)
+    const uint32_t w_first = e_unit / 16u + threadIdx.x;
+    const uint32_t widx = w_first < ad.k ? w_first : ad.k - 1u;
+    const int G4 = (W + 3) / 4;  // <= 4 kTS
+    const int32_t* tt = tabs + (size_t)t * kTernTab;
+    uint32_t wv[16 * kTS];
+#pragma unroll
+    for (int k = 0; k < 16 * kTS; ++k) wv[k] = gp(w_a(wp, k < W ? k : W - 1) + ad.off)[widx];
+    for (int x = 4 * (int)threadIdx.x; x < 256 * G4; x += 4 * kBlock)
+        *reinterpret_cast<u32x4*>(tab_sh + x) = ldg4u(tt + x);
+    __syncthreads();
+    int32_t S[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) S[q] = 0;
+#pragma unroll
+    for (int g = 0; g < 4 * kTS; ++g) {
+        if (g < G4) {
+            const uint32_t xw[4] = {wv[4 * g], wv[4 * g + 1], wv[4 * g + 2], wv[4 * g + 3]};
+            uint32_t y[4];
+            tern_indices(xw, y);
+            const int32_t* tg = tab_sh + 256 * g;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) S[4 * j + i] += tg[(y[j] >> (8 * i)) & 255u];
+        }
+    }
+    // exact: |S| < 2^31 and the unit is a power of two
+    const double unit = __builtin_ldexp(1.0, (int)((inf >> 8) & 255u) - 150);
+    float res[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) res[q] = alpha * (float)((double)S[q] * unit);
+    float* stage = reinterpret_cast<float*>(tab_sh);
+    __syncthreads();  // every wave is past its lookups
+    stage_results(stage, res);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const uint32_t e = e_unit + 1024u * k + 4u * threadIdx.x;
+        store_group(ad, e, staged_piece(stage, k));
     }
 }
 
@@ -825,16 +856,14 @@ hipError_t launch_aggregate_quant(int bits, const ADesc* a, int T, uint32_t U, c
         const uint32_t* ci = info;
         const int32_t* ct = tabs;
         const int steps = W > 64 ? 1 : (W + 15) / 16;
-        if (steps <= 1) return launch_timed(kTimedAggQuant, aggregate_quant<2, 1>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
-        if (steps == 2) return launch_timed(kTimedAggQuant, aggregate_quant<2, 2>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
-        if (steps == 3) return launch_timed(kTimedAggQuant, aggregate_quant<2, 3>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
-        return launch_timed(kTimedAggQuant, aggregate_quant<2, 4>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
+        if (steps <= 1) return launch_timed(kTimedAggQuant, aggregate_tern<1>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
+        if (steps == 2) return launch_timed(kTimedAggQuant, aggregate_tern<2>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
+        if (steps == 3) return launch_timed(kTimedAggQuant, aggregate_tern<3>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
+        return launch_timed(kTimedAggQuant, aggregate_tern<4>, grid, block, 0, s, a, T, U, wp, W, alpha, ci, ct);
     }
-    const uint32_t* nul = nullptr;
-    const int32_t* nt = nullptr;
     if (bits == 4)
-        return launch_timed(kTimedAggQuant, aggregate_quant<4, 1>, grid, block, 0, s, a, T, U, wp, W, alpha, nul, nt);
-    return launch_timed(kTimedAggQuant, aggregate_quant<8, 1>, grid, block, 0, s, a, T, U, wp, W, alpha, nul, nt);
+        return launch_timed(kTimedAggQuant, aggregate_quant<4>, grid, block, 0, s, a, T, U, wp, W, alpha);
+    return launch_timed(kTimedAggQuant, aggregate_quant<8>, grid, block, 0, s, a, T, U, wp, W, alpha);
 }
 
 }  // namespace bc
