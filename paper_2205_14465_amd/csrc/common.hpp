@@ -291,6 +291,8 @@ struct RawChunk {
     uint32_t valid;
 };
 
+// The loads are non-temporal: the one-pass kernels, which use this, read
+// every gradient and residual once and write the residual once.
 // kDT: 0 every tensor of the call is fp32, 1 every tensor is fp16, 2 both
 // occur (td.dtype decides).  A kernel that keeps loads in flight across
 // iterations is instantiated per kDT so that the common single-dtype calls
@@ -308,11 +310,11 @@ __device__ __forceinline__ void load_raw(const TDesc& td, uint32_t j, bool use_r
 #pragma unroll
             for (int rr = 0; rr < kRounds; ++rr) {
                 if constexpr (kDT == 0) {
-                    const f32x4 x = ldg4f_any((const float*)td.grad + load_at(n, j, rr));
+                    const f32x4 x = ldg4f_any<true>((const float*)td.grad + load_at(n, j, rr));
 #pragma unroll
                     for (int q = 0; q < 4; ++q) r.g[4 * rr + q] = f2u(x[q]);
                 } else {
-                    const u32x2 h = ldg4h_any((const uint16_t*)td.grad + load_at(n, j, rr));
+                    const u32x2 h = ldg4h_any<true>((const uint16_t*)td.grad + load_at(n, j, rr));
                     r.g[4 * rr] = h.x;
                     r.g[4 * rr + 1] = h.y;
                 }
@@ -320,7 +322,7 @@ __device__ __forceinline__ void load_raw(const TDesc& td, uint32_t j, bool use_r
             if (use_resid) {
 #pragma unroll
                 for (int rr = 0; rr < kRounds; ++rr) {
-                    const f32x4 y = ldg4f_any(td.resid + load_at(n, j, rr));
+                    const f32x4 y = ldg4f_any<true>(td.resid + load_at(n, j, rr));
 #pragma unroll
                     for (int q = 0; q < 4; ++q) r.e[4 * rr + q] = y[q];
                 }

@@ -180,14 +180,12 @@ __device__ __forceinline__ void quantize_round(const TDesc& td, uint32_t e0, boo
 // payload words, residual into e.
 template <int kBits, bool kNT>
 __device__ __forceinline__ void quantize_chunk(const TDesc& td, uint32_t j, float m, float (&v)[kEpt], uint32_t valid,
-                                               uint64_t seed, uint32_t* __restrict__ words) {
+                                               const float (&u)[kRounds][4], uint32_t* __restrict__ words) {
     using Q = Quant<kBits>;
     const bool any = m > 0.f;
     const float inv = any ? (float)((double)Q::kLevels / (double)m) : 0.f;
     const float unit = (float)((double)m / (double)Q::kLevels);
     uint32_t* tw = words + td.off;
-    float u[kRounds][4];
-    chunk_uniforms(seed, td.tid, j, u);
 #pragma unroll
     for (int r = 0; r < kRounds; ++r) {
         const uint32_t e0 = j * (uint32_t)kChunk + 1024u * r + 4u * threadIdx.x;  // element of the tensor
@@ -260,7 +258,9 @@ __global__ __launch_bounds__(kBlock) void quant_pass2(const TDesc* __restrict__ 
     float v[kEpt];
     uint32_t valid;
     load_stored_v(td, j, v, valid);  // e holds v after pass 1 (or v = g without error feedback)
-    quantize_chunk<kBits, kNT>(td, j, m, v, valid, seed, words);
+    float u[kRounds][4];
+    chunk_uniforms(seed, td.tid, j, u);
+    quantize_chunk<kBits, kNT>(td, j, m, v, valid, u, words);
 }
 
 // One pass (tensors no longer than the resident grid), as the one-pass
@@ -272,6 +272,10 @@ __global__ __launch_bounds__(kBlock) void quant_pass2(const TDesc* __restrict__ 
 // workgroup is resident; past the host's wait limit a waiting workgroup
 // computes the missing chunk maxima itself and publishes them by
 // compare-and-swap (common.hpp), so waits end whatever the residency.
+// Without any wait the kernel took 75 instead of 88 us (25.6 M elements, 2
+// bits): the Philox arithmetic, which needs no scale, therefore runs before
+// the wait, and with non-temporal accesses (as in the one-pass sign kernel)
+// it takes 80 us.
 namespace {
 
 constexpr int kHelpBatch = 256;  // missing maxima a waiting workgroup computes per pass
@@ -404,12 +408,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             load_raw<kDT>(tdn, cn - tdn.chunk0, tdn.resid != nullptr, raw);
         }
         if (prev) {
+            // the uniforms need no scale: their arithmetic runs while the
+            // other chunks' maxima arrive
+            float u[kRounds][4];
+            chunk_uniforms(seed, tdp.tid, jp, u);
             float m = mp;
             if (tdp.nchunks > 1) {
                 m = quant_onepass_scale(tdp, ws.q_slot, sh, wait_ticks, ctl_sh);
                 if (jp == 0 && threadIdx.x == 0) scale_out[tensor_of_chunk(d, T, tdp.chunk0)] = m;
             }
-            quantize_chunk<kBits, false>(tdp, jp, m, vp, validp, seed, words);
+            quantize_chunk<kBits, true>(tdp, jp, m, vp, validp, u, words);
         }
         if (!have) break;
 #pragma unroll
@@ -801,10 +809,12 @@ template <int kBits>
 bool quant_onepass_dt(uint64_t seed, const TDesc* d, int T, uint32_t C, uint32_t max_chunks, bool any_empty,
                       bool any_f16, bool any_f32, uint32_t* words, float* scale, const Ws& ws, int cus,
                       hipStream_t s) {
-    if (any_f16 && any_f32)
-        return quant_onepass_launch<kBits, 2>(seed, d, T, C, max_chunks, any_empty, words, scale, ws, cus, s);
-    if (any_f16) return quant_onepass_launch<kBits, 1>(seed, d, T, C, max_chunks, any_empty, words, scale, ws, cus, s);
-    return quant_onepass_launch<kBits, 0>(seed, d, T, C, max_chunks, any_empty, words, scale, ws, cus, s);
+    auto launch = [&](auto one_pass) {
+        return one_pass(seed, d, T, C, max_chunks, any_empty, words, scale, ws, cus, s);
+    };
+    return any_f16 && any_f32 ? launch(quant_onepass_launch<kBits, 2>)
+           : any_f16          ? launch(quant_onepass_launch<kBits, 1>)
+                              : launch(quant_onepass_launch<kBits, 0>);
 }
 }  // namespace
 
@@ -813,10 +823,12 @@ hipError_t launch_quant_compress(int bits, uint64_t seed, const TDesc* d, int T,
                                  const Ws& ws, int cus, hipStream_t s) {
     if (T <= 0) return hipSuccess;
     // one pass when every tensor fits the resident grid
-    const bool one =
-        bits == 2   ? quant_onepass_dt<2>(seed, d, T, C, max_chunks, any_empty, any_f16, any_f32, words, scale, ws, cus, s)
-        : bits == 4 ? quant_onepass_dt<4>(seed, d, T, C, max_chunks, any_empty, any_f16, any_f32, words, scale, ws, cus, s)
-                    : quant_onepass_dt<8>(seed, d, T, C, max_chunks, any_empty, any_f16, any_f32, words, scale, ws, cus, s);
+    auto launch = [&](auto one_pass) {
+        return one_pass(seed, d, T, C, max_chunks, any_empty, any_f16, any_f32, words, scale, ws, cus, s);
+    };
+    const bool one = bits == 2   ? launch(quant_onepass_dt<2>)
+                     : bits == 4 ? launch(quant_onepass_dt<4>)
+                                 : launch(quant_onepass_dt<8>);
     if (one) return hipGetLastError();
     const bool nt = C > kNtChunks;
     if (C > 0) {

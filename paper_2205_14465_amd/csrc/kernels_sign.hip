@@ -17,6 +17,11 @@
 // run: pass 1 writes the
 // bits, the chunk partial sums and v (into e); pass 2 sums the partials of
 // its tensor in the same fixed order, re-reads v and writes the residual.
+// The one-pass kernel's accesses are non-temporal at every size: lists of 300
+// to 15000 chunks took between 3% more and 15% less than with cached ones
+// (5662 chunks: 57 against 55 us with one set of buffers in turn, 58 against
+// 68 with three; 14963 chunks: 138 against 162), ResNet-50's kernel 58
+// against 68 us (5.3 TB/s).
 // (An earlier one-pass form that waited for each chunk's own tensor before
 // moving on was slower than two passes: the workgroups of a tensor waited
 // for each other with nothing to overlap.)
@@ -299,7 +304,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1
                 s = onepass_scale(tdp, ws.s_slot, sh, wait_ticks, ctl_sh);
                 if (jp == 0 && threadIdx.x == 0) scale_out[tensor_of_chunk(d, T, tdp.chunk0)] = s;
             }
-            if (tdp.resid) store_sign_residual<false>(tdp, jp, s, vp);
+            if (tdp.resid) store_sign_residual<true>(tdp, jp, s, vp);
         }
         if (!have) break;
 #pragma unroll
