@@ -78,7 +78,7 @@ __device__ __forceinline__ void entry_tensor_advance(const TDesc* __restrict__ d
     entry_tensor_load(d, T, keys, t, et);
 }
 
-// Generate the indices of kGenEntries consecutive payload entries, keep
+// Generate the indices of kGenBlock * per_thread consecutive payload entries, keep
 // them in gen (the payload's index buffer), and write this workgroup's row
 // of bucket counts.  A thread
 // takes its entries in turn, but the cycle walks are not aligned across the
@@ -89,12 +89,12 @@ __device__ __forceinline__ void entry_tensor_advance(const TDesc* __restrict__ d
 // largest walk in the wave (walks take 1 to 4 evaluations on average and
 // have long tails).
 __global__ __launch_bounds__(kGenBlock) void randk_count(const TDesc* __restrict__ d, int T, uint64_t sum_k,
-                                                         uint32_t S, uint32_t NB, uint32_t* __restrict__ gen,
-                                                         Ws ws) {
+                                                         uint32_t S, uint32_t NB, int per_thread,
+                                                         uint32_t* __restrict__ gen, Ws ws) {
     extern __shared__ uint32_t hist[];  // [NB]
     for (uint32_t b = threadIdx.x; b < NB; b += kGenBlock) hist[b] = 0;
     __syncthreads();
-    const uint64_t j0 = (uint64_t)blockIdx.x * kGenEntries + threadIdx.x;
+    const uint64_t j0 = (uint64_t)blockIdx.x * (uint32_t)(kGenBlock * per_thread) + threadIdx.x;
     EntryTensor et;
     uint64_t j = j0;
     int q = 0;
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kGenBlock) void randk_count(const TDesc* __restrict
                 atomicAdd(&hist[(et.chunk0 + x / (uint32_t)kChunk) >> S], 1u);
                 ++q;
                 j += (uint64_t)kGenBlock;
-                live = q < kGenPerThread && j < sum_k;
+                live = q < per_thread && j < sum_k;
                 if (live) {
                     entry_tensor_advance(d, T, ws.r_keys, j, et);
                     cur = (uint32_t)(j - et.off);
@@ -205,7 +205,7 @@ __global__ __launch_bounds__(kBlock) void randk_scan_apply(uint32_t NB, Ws ws, c
 // column prefix) plus a rank taken in LDS.  The value stored is the index's
 // position within the bucket's 2^S chunks.
 __global__ __launch_bounds__(kGenBlock) void randk_place(const TDesc* __restrict__ d, int T, uint64_t sum_k,
-                                                         uint32_t S, uint32_t NB,
+                                                         uint32_t S, uint32_t NB, int per_thread,
                                                          const uint32_t* __restrict__ gen, Ws ws) {
     extern __shared__ uint32_t lds[];
     uint32_t* base = lds;       // [NB] this workgroup's first position in each bucket
@@ -216,10 +216,10 @@ __global__ __launch_bounds__(kGenBlock) void randk_place(const TDesc* __restrict
         rank[b] = 0;
     }
     __syncthreads();
-    const uint64_t j0 = (uint64_t)blockIdx.x * kGenEntries + threadIdx.x;
+    const uint64_t j0 = (uint64_t)blockIdx.x * (uint32_t)(kGenBlock * per_thread) + threadIdx.x;
     EntryTensor et;
     if (j0 < sum_k) entry_tensor_load(d, T, ws.r_keys, tensor_of_entry(d, T, j0), et);
-    for (int q = 0; q < kGenPerThread; ++q) {
+    for (int q = 0; q < per_thread; ++q) {
         const uint64_t j = j0 + (uint64_t)q * kGenBlock;
         if (j >= sum_k) break;
         entry_tensor_advance(d, T, ws.r_keys, j, et);
@@ -595,18 +595,33 @@ hipError_t launch_randk(uint64_t seed, const TDesc* d, int T, uint32_t C, uint64
     const dim3 blk(kBlock);
     const uint32_t nscan = (NB + kScanBlock - 1) / kScanBlock;
     uint64_t* bsum = ws.r_coff + (size_t)NB + 1;  // scratch after the bucket offsets
-    hipLaunchKernelGGL(randk_prep, dim3((T + 255) / 256), dim3(256), 0, s, d, T, seed, ws);
-    const uint32_t nblk = (uint32_t)((sum_k + kGenEntries - 1) / kGenEntries);
-    if (nblk) {
-        hipLaunchKernelGGL(randk_count, dim3(nblk), dim3(kGenBlock), (size_t)NB * 4, s, d, T, sum_k, S, NB, idx,
-                           ws);
+    // Entries per generating thread: few enough that up to 512 workgroups
+    // share the work (with 32 each, one workgroup generated the 30 thousand
+    // entries of a 3 M-element list alone: 290 us for 150 tensors, 21 now).
+    // More workgroups have more rows of bucket counts than the workspace
+    // plans for; they go into the payload's values, which only the stream
+    // pass writes, and must fit there.
+    int per_thread = kGenPerThread;
+    uint32_t nblk = (uint32_t)((sum_k + kGenEntries - 1) / kGenEntries);
+    Ws wg = ws;
+    for (int half = kGenPerThread / 2; half >= 1; half /= 2) {
+        const uint64_t more = (sum_k + (uint64_t)kGenBlock * half - 1) / ((uint64_t)kGenBlock * half);
+        if (more > 512 || more * NB > sum_k) break;
+        per_thread = half;
+        nblk = (uint32_t)more;
+        wg.r_hist = (uint32_t*)val;
     }
-    hipLaunchKernelGGL(randk_columns, dim3((NB + 63) / 64), dim3(kColBlock), 0, s, NB, nblk, ws);
+    hipLaunchKernelGGL(randk_prep, dim3((T + 255) / 256), dim3(256), 0, s, d, T, seed, ws);
+    if (nblk) {
+        hipLaunchKernelGGL(randk_count, dim3(nblk), dim3(kGenBlock), (size_t)NB * 4, s, d, T, sum_k, S, NB,
+                           per_thread, idx, wg);
+    }
+    hipLaunchKernelGGL(randk_columns, dim3((NB + 63) / 64), dim3(kColBlock), 0, s, NB, nblk, wg);
     hipLaunchKernelGGL(randk_scan_sums, dim3(nscan), blk, 0, s, NB, ws, bsum);
     hipLaunchKernelGGL(randk_scan_apply, dim3(nscan), blk, 0, s, NB, ws, bsum);
     if (nblk)
         hipLaunchKernelGGL(randk_place, dim3(nblk), dim3(kGenBlock), lds_place, s, d, T, sum_k, S, NB,
-                           (const uint32_t*)idx, ws);
+                           per_thread, (const uint32_t*)idx, wg);
     // ids in groups of 8F: 8 buckets' F runs each (a last group may hold
     // fewer buckets: its surplus workgroups return at once)
     const uint32_t F = 1u << (S - SP);

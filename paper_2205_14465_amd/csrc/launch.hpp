@@ -207,7 +207,7 @@ hipError_t launch_dgc_clip(const TDesc* d, int T, uint32_t C, double clip, doubl
 hipError_t launch_aggregate_quant(int bits, const ADesc* a, int T, uint32_t units, const uint64_t* wp, int W,
                                   float alpha, uint32_t* info, int32_t* tabs, hipStream_t s);
 
-// Random-k bucketing: generating workgroups of kGenBlock threads handle
+// Random-k bucketing: generating workgroups of kGenBlock threads handle up to
 // kGenEntries payload entries each; a bucket is 2^S consecutive chunks with
 // S the smallest shift giving at most kRandkBuckets buckets (S <= 8).  A
 // call whose chunk count would need more than kRandkMaxBuckets buckets is

@@ -270,6 +270,19 @@ def test_randk_bucket_split_into_runs(case):
     assert_resid_equal(got_e, want_e)
 
 
+@pytest.mark.parametrize("ns,ratio", [([3_000_000], 0.01), ([200] * 900 + [1_500_001], 0.01),
+                                      ([2_000_000] * 2, 1e-4), ([5_000_000], 0.05), ([4096] * 30, 1.0)])
+def test_randk_generating_workgroups(ns, ratio):
+    """Entries per generating thread from 1 to 32: counts kept in the
+    payload's values, and (few entries in many chunks) in the workspace."""
+    rng = np.random.default_rng(len(ns))
+    grads, resids = make_set(ns, rng)
+    got, got_e = gpu_compress("randk", ratio, SEED, grads, resids)
+    want, want_e = O.compress_set("randk", ratio, SEED, grads, resids)
+    assert_sparse_equal(got, want, ns)
+    assert_resid_equal(got_e, want_e)
+
+
 def test_randk_tensor_id_keys_the_stream():
     rng = np.random.default_rng(15)
     ns = [50000, 50000]
