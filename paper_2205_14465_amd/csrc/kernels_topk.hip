@@ -436,9 +436,22 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
     ws.t_zero[t] = zero;
 }
 
+// Stores and a wait by which a workgroup hands data to others of the same
+// kernel: the stores go through to where every compute die sees them, so the
+// hand-over needs no release (which writes back the die's whole L2 cache,
+// about 9 us, one workgroup after another).
+__device__ __forceinline__ void put_agent(uint32_t* p, uint32_t x) {
+    __hip_atomic_store((BC_GLOBAL uint32_t*)p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// Loads that follow see what other workgroups handed over.
+__device__ __forceinline__ void acquire_agent() { __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); }
+
 // Read (and clear) the eight bins under `hi` of a tensor's histogram, all
 // copies added, highest bin first.  Whole vectors: with single words, lanes
 // 32 bytes apart, the clearing stores bound a find (12 us at T = 199).
+// kInPass: the histogram is used again by other workgroups of the same kernel.
+template <bool kInPass>
 __device__ __forceinline__ void take_bins(uint32_t* gh, int hi, int copies, uint32_t (&h)[8]) {
     constexpr int stride = kBins0, kMax = kGeneralCopiesMax;
     u32x4 a[kMax], b[kMax];
@@ -460,18 +473,24 @@ __device__ __forceinline__ void take_bins(uint32_t* gh, int hi, int copies, uint
             h[4 + q] += b[r][3 - q];
         }
         if (r < copies) {
-            *(BC_GLOBAL u32x4*)(gh + r * stride + hi - 4) = u32x4{0u, 0u, 0u, 0u};
-            *(BC_GLOBAL u32x4*)(gh + r * stride + hi - 8) = u32x4{0u, 0u, 0u, 0u};
+            if constexpr (kInPass) {
+#pragma unroll
+                for (int q = 1; q <= 8; ++q) put_agent(gh + r * stride + hi - q, 0u);
+            } else {
+                *(BC_GLOBAL u32x4*)(gh + r * stride + hi - 4) = u32x4{0u, 0u, 0u, 0u};
+                *(BC_GLOBAL u32x4*)(gh + r * stride + hi - 8) = u32x4{0u, 0u, 0u, 0u};
+            }
         }
     }
 }
 
 // The exact candidate threshold of a tensor, the bin of the k-th key in its
 // histogram of key bits 30..20, by a whole workgroup.
+template <bool kInPass>
 __device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh) {
     const int hi = kBins0 - threadIdx.x * 8;  // thread i owns the i-th eight bins from the top
     uint32_t h[8];
-    take_bins(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
+    take_bins<kInPass>(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
     uint32_t mine = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q) mine += h[q];
@@ -480,8 +499,14 @@ __device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, con
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
         if (above < td.k && td.k <= above + h[q]) {
-            ws.t_thr[t] = (uint32_t)(hi - 1 - q) << 20 | kExactShift;
-            ws.t_zero[t] = kNoEarlyZero;  // e_new is already written
+            const uint32_t thr = (uint32_t)(hi - 1 - q) << 20 | kExactShift;
+            if constexpr (kInPass) {
+                put_agent(ws.t_thr + t, thr);
+                put_agent(ws.t_zero + t, kNoEarlyZero);
+            } else {
+                ws.t_thr[t] = thr;
+                ws.t_zero[t] = kNoEarlyZero;  // e_new is already written
+            }
         }
         above += h[q];
     }
@@ -494,7 +519,7 @@ __device__ __forceinline__ bool find_bin(const TDesc& td, int t, int copies, con
                                          uint32_t* found) {
     const int hi = kBins0 - threadIdx.x * 8;
     uint32_t h[8];
-    take_bins(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
+    take_bins<false>(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
     if (threadIdx.x == 0) found[0] = (uint32_t)kBins0 - 1u;
     uint32_t mine = 0;
 #pragma unroll
@@ -521,7 +546,7 @@ __device__ __forceinline__ bool find_bin(const TDesc& td, int t, int copies, con
 __global__ __launch_bounds__(kBlock) void topk_find_thr(const TDesc* __restrict__ d, int copies, Ws ws) {
     __shared__ uint64_t sh[4];
     const TDesc td = d[blockIdx.x];
-    if (td.k) find_thr(td, (int)blockIdx.x, copies, ws, sh);
+    if (td.k) find_thr<false>(td, (int)blockIdx.x, copies, ws, sh);
 }
 
 __global__ __launch_bounds__(kBlock) void topk_find_bin(const TDesc* __restrict__ d, int copies, Ws ws) {
@@ -533,7 +558,12 @@ __global__ __launch_bounds__(kBlock) void topk_find_bin(const TDesc* __restrict_
     const bool ok = find_bin(td, t, copies, ws, sh, found);
     if (threadIdx.x != 0) return;
     ws.t_fb[t] = ok ? 0u : 1u;  // bytecomp_topk_stats counts them
-    if (!ok) atomicOr(ws.t_any, 1u);
+    if (ok) return;
+    // one entry of the fallback's list: the tensor, and how many chunks the
+    // entries before it have (t_krem and t_prefix count its finished chunks)
+    ws.t_krem[t] = ws.t_prefix[t] = 0u;
+    const unsigned long long at = atomicAdd((unsigned long long*)ws.t_any, 1ull << 32 | td.nchunks);
+    ws.t_off[at >> 32] = (uint64_t)t << 32 | (uint32_t)at;
 }
 
 // Candidate compaction.  kStream (sampled main pass): v = g + e,
@@ -655,83 +685,109 @@ __global__ __launch_bounds__(kBlock) void topk_compact(
     compact_chunk<kNT, kDGC, kStream>(td, t, blockIdx.x, copies, ws, f, l, list_u);
 }
 
-// The exact path for the tensors that find_bin flagged, in one launch that
-// ends at once when there are none (the usual case).  Workgroups claim chunks
-// one at a time: first every flagged chunk gets back what the stream pass
-// zeroed early and adds its keys to the tensor's histogram of bits 30..20;
-// whoever finishes the last one finds the exact thresholds; then every
-// flagged chunk is compacted again, and whoever finishes the last finds the
-// bins.  A workgroup waits only between the two, when every chunk is claimed
-// by a workgroup that runs and waits for nothing, so the wait ends whatever
-// part of the grid is resident.
+// The exact path for the tensors that find_bin listed, in one launch that
+// ends at once when there are none (the usual case).  Only the listed tensors'
+// chunks are visited.  Workgroups claim batches of consecutive ones, first
+// all batches of the first pass, then all of the second: in the first the
+// chunks get back what the stream pass zeroed early and add their keys to
+// their tensor's histogram of bits 30..20, and whoever finishes a tensor's
+// last chunk finds its exact threshold; in the second they are compacted
+// again, and whoever finishes the last finds the bin.  A workgroup waits only
+// in the second pass, for a threshold whose chunks are all claimed by
+// workgroups that run and wait for nothing, so the wait ends whatever part of
+// the grid is resident.  The two counters are paid once per batch and tensor,
+// and what other workgroups read goes out by put_agent (one listed tensor of
+// BERT-base cost 3.3 ms when all chunks of the call were visited one by one
+// with a release each).
 template <bool kDGC>
-__global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict__ d, int T, uint32_t C, int copies,
-                                                        Ws ws) {
+__global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict__ d, int copies, Ws ws) {
     __shared__ CompactLds l;
-    __shared__ uint32_t claim, found[2];
-    uint32_t* ctl = ws.t_any;  // 1, 2: chunks claimed and done (histogram); 3: thresholds found; 4, 5: as 1, 2 (compaction)
-    if (ctl[0] == 0u) return;
+    __shared__ uint32_t word, found[2];
+    const uint64_t any = *(const uint64_t*)ws.t_any;  // listed tensors, and their chunks
+    if (any == 0) return;
+    const uint32_t listed = (uint32_t)(any >> 32), F = (uint32_t)any;
+    const uint32_t batch = (F + gridDim.x - 1u) / gridDim.x;
+    const uint32_t batches = (F + batch - 1u) / batch;
     const DgcFuse none{nullptr, 0.f, nullptr};
-    for (int phase = 0; phase < 2; ++phase) {
-        for (;;) {
-            if (threadIdx.x == 0) claim = atomicAdd(ctl + 1 + 3 * phase, 1u);
-            __syncthreads();
-            const uint32_t c = claim;
-            if (c >= C) break;
-            const int t = tensor_of_chunk(d, T, c);
+    for (;;) {
+        __syncthreads();  // every thread has read `word`
+        if (threadIdx.x == 0) word = atomicAdd(ws.t_any + 2, 1u);
+        __syncthreads();
+        const uint32_t q = word;
+        if (q >= 2u * batches) return;
+        const bool second = q >= batches;
+        uint32_t f = (second ? q - batches : q) * batch;
+        const uint32_t f1 = f + batch < F ? f + batch : F;
+        uint32_t i = 0, hi = listed - 1u;  // the last entry that starts at or before chunk f of the list
+        while (i < hi) {
+            const uint32_t mid = (i + hi + 1u) >> 1;
+            if ((uint32_t)ws.t_off[mid] <= f) i = mid; else hi = mid - 1u;
+        }
+        for (; f < f1; ++i) {
+            const int t = (int)(ws.t_off[i] >> 32);
             const TDesc td = d[t];
-            if (ws.t_fb[t] != 0u && phase == 0) {
+            const uint32_t j0 = f - (uint32_t)ws.t_off[i];
+            const uint32_t j1 = j0 + (f1 - f) < td.nchunks ? j0 + (f1 - f) : td.nchunks;
+            f += j1 - j0;
+            if (!second) {
                 for (int b = threadIdx.x; b < kBins0; b += kBlock) l.lh[b] = 0;
-                const uint32_t m = ws.t_ccount[c], zero = ws.t_zero[t];
-                if (td.resid && (!kDGC || m <= kListMax)) {
-                    for (uint32_t i = threadIdx.x; i < m; i += kBlock) {
-                        const uint2 e = ws.t_cand[(size_t)c * kChunk + cand_at(c, m, i)];
-                        if ((e.y & 0x7FFFFFFFu) >= zero) {
-                            gp(td.resid)[e.x] = u2f(e.y);
-                            if constexpr (kDGC) gp(vel_of(td))[e.x] = *cand_vel(ws, c, i);
+                const uint32_t zero = ws.t_zero[t];
+                for (uint32_t c = td.chunk0 + j0; c < td.chunk0 + j1; ++c) {
+                    const uint32_t m = ws.t_ccount[c];
+                    if (td.resid && zero != kNoEarlyZero && (!kDGC || m <= kListMax)) {
+                        const uint2* cand = ws.t_cand + (size_t)c * kChunk;
+                        constexpr uint32_t kU = 4;  // a thread's loads in flight together
+                        for (uint32_t r0 = threadIdx.x; r0 < m; r0 += kU * kBlock) {
+                            uint2 e[kU];
+#pragma unroll
+                            for (uint32_t u = 0; u < kU; ++u) {
+                                const uint32_t r = r0 + u * kBlock;
+                                e[u] = r < m ? cand[cand_at(c, m, r)] : make_uint2(0, 0);
+                            }
+#pragma unroll
+                            for (uint32_t u = 0; u < kU; ++u) {
+                                const uint32_t r = r0 + u * kBlock;
+                                if (r >= m || (e[u].y & 0x7FFFFFFFu) < zero) continue;
+                                put_agent((uint32_t*)td.resid + e[u].x, e[u].y);
+                                if constexpr (kDGC) put_agent((uint32_t*)vel_of(td) + e[u].x, f2u(*cand_vel(ws, c, r)));
+                            }
                         }
                     }
+                    stores_done();
+                    __syncthreads();  // this workgroup re-reads the chunk
+                    float v[kEpt];
+                    uint32_t valid;
+                    load_stored_v(td, c - td.chunk0, v, valid);
+                    add_keys(l.lh, v, valid);
                 }
-                __syncthreads();  // this workgroup re-reads the chunk
-                float v[kEpt];
-                uint32_t valid;
-                load_stored_v(td, c - td.chunk0, v, valid);
-                add_keys(l.lh, v, valid);
                 __syncthreads();
-                flush_hist(l.lh, ws.t_hist + ((size_t)t * copies + c % (uint32_t)copies) * kBins0, kBins0);
-            } else if (ws.t_fb[t] != 0u) {
-                compact_chunk<false, false, false>(td, t, c, copies, ws, none, l, nullptr);
-            }
-            __threadfence();  // before the chunk counts as done
-            __syncthreads();
-            if (threadIdx.x == 0) claim = atomicAdd(ctl + 2 + 3 * phase, 1u);
-            __syncthreads();
-            const bool last = claim == C - 1u;
-            __syncthreads();
-            if (!last) continue;
-            __threadfence();  // the others' histograms
-            for (int q0 = 0; q0 < T; q0 += kBlock) {
-                const int mine = q0 + (int)threadIdx.x;
-                if (!__syncthreads_or(mine < T && d[mine].k != 0u && ws.t_fb[mine] != 0u)) continue;
-                for (int q = q0; q < T && q < q0 + kBlock; ++q) {
-                    const TDesc tq = d[q];
-                    if (tq.k == 0 || ws.t_fb[q] == 0u) continue;
-                    if (phase == 0) find_thr(tq, q, copies, ws, l.sh);
-                    else (void)find_bin(tq, q, copies, ws, l.sh, found);
-                    __syncthreads();
+                flush_hist(l.lh, ws.t_hist + ((size_t)t * copies + f % (uint32_t)copies) * kBins0, kBins0);
+            } else {
+                if (threadIdx.x == 0)
+                    while (__hip_atomic_load(ws.t_fb + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2u)
+                        __builtin_amdgcn_s_sleep(8);
+                __syncthreads();
+                acquire_agent();  // threshold and restored values written elsewhere
+                for (uint32_t c = td.chunk0 + j0; c < td.chunk0 + j1; ++c) {
+                    compact_chunk<false, false, false>(td, t, c, copies, ws, none, l, nullptr);
+                    __syncthreads();  // the next one clears the histogram
                 }
             }
-            __threadfence();
+            stores_done();  // before the chunks count as done
             __syncthreads();
-            if (phase == 0 && threadIdx.x == 0)
-                __hip_atomic_store(ctl + 3, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            if (threadIdx.x == 0) word = atomicAdd(second ? ws.t_prefix + t : ws.t_krem + t, j1 - j0) + (j1 - j0);
+            __syncthreads();
+            if (word != td.nchunks) continue;
+            acquire_agent();  // the others' histograms
+            if (second) {
+                (void)find_bin(td, t, copies, ws, l.sh, found);
+            } else {
+                find_thr<true>(td, t, copies, ws, l.sh);
+                stores_done();
+                __syncthreads();
+                if (threadIdx.x == 0) put_agent(ws.t_fb + t, 2u);
+            }
         }
-        if (phase == 1) return;
-        if (threadIdx.x == 0)
-            while (__hip_atomic_load(ctl + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u)
-                __builtin_amdgcn_s_sleep(8);
-        __syncthreads();
-        __threadfence();  // thresholds and restored values written elsewhere
     }
 }
 
@@ -1484,7 +1540,7 @@ hipError_t launch_topk_t(int kind, double ratio, uint64_t seed, const TDesc* d, 
             (void)launch_timed(kTimedTopkCompact, topk_compact<false, kDGC, true>, dim3(C), blk, 0, s, d, T, R, ws,
                                f);
         hipLaunchKernelGGL(topk_find_bin, dim3(T), blk, 0, s, d, R, ws);
-        hipLaunchKernelGGL(topk_fallback<kDGC>, dim3(C < 1024u ? C : 1024u), blk, 0, s, d, T, C, R, ws);
+        hipLaunchKernelGGL(topk_fallback<kDGC>, dim3(C < 1024u ? C : 1024u), blk, 0, s, d, R, ws);
     }
     if (C >= kCountBatchFrom)
         hipLaunchKernelGGL(topk_cand_count<4>, dim3((C + 15) / 16), blk, 0, s, d, T, C, R, ws);

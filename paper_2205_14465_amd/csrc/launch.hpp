@@ -37,13 +37,15 @@ struct Ws {
                             // after the histograms' copies, inside t_hist)
     uint32_t* t_prefix;     // [T] radix-select prefix, then the k-th key
     uint32_t* t_krem;       // [T] entries still to select
-    uint32_t* t_fb;         // [T] 1 = tensor needs the exact-histogram fallback
-    uint32_t* t_any;        // [kAnyWords] nonzero when some tensor of the call needs it; the fallback's counters
+    uint32_t* t_fb;         // [T] nonzero: the tensor takes the exact-histogram fallback (2: its threshold is found)
+    uint32_t* t_any;        // [kAnyWords] one 64-bit word, the tensors listed for the fallback (high half) and
+                            // their chunks (low half), then its claims
     uint2* t_cand;          // [C * 4096] candidates (local index, value bits)
     uint32_t* t_ccount;     // [C] candidates per chunk
     uint32_t* t_gt;         // [C] candidates above the k-th key's bin
     uint32_t* t_eq;         // [C] candidates inside it
-    uint64_t* t_off;        // [C] their low bits, then the payload position of a chunk's first winner
+    uint64_t* t_off;        // [C] the fallback's list, then the low bits of the candidates inside the k-th
+                            // key's bin, then the payload position of a chunk's first winner
     uint32_t* t_eqb;        // [C] equal-key candidates in earlier chunks
     // BC_RANDK
     uint32_t* r_keys;       // [T * 4] Feistel round keys
@@ -116,7 +118,7 @@ bool take_kernel_timer(int k, hipEvent_t* start, hipEvent_t* stop);
 // a one-pass compress workgroup waits for the rest of its tensor's chunk
 // partials before it computes the missing ones itself.
 uint32_t onepass_wait_ticks();
-constexpr uint32_t kAnyWords = 6;
+constexpr uint32_t kAnyWords = 3;
 // Copies of each top-k histogram in the general pipeline for a call of T
 // tensors: workgroups add into copy (their index mod copies), which spreads
 // the atomic additions to the busiest bins; readers add the copies.

@@ -256,3 +256,46 @@ def test_dgc_randk_many_chunks():
         got_u = torch.cat([x for x in du if x.numel()]).cpu().numpy()
         assert np.array_equal(bits(got_e), bits(np.concatenate(e))), step
         assert np.array_equal(bits(got_u), bits(np.concatenate(u))), step
+
+
+def test_topk_fallback_costs_its_tensor():
+    """One tensor of 74 chunks whose sample misleads, in a call of 22 thousand
+    chunks: its exact path visits its own chunks only.  That takes two short
+    passes (tens of microseconds); visiting every chunk of the call took
+    milliseconds, so the bound of 0.5 ms over the same call without the
+    tensor's fallback separates the two by far."""
+    import torch
+    from paper_2205_14465_amd import binding as B
+    ns = [1_500_000] * 60 + [300_001]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    grads = [torch.randn(n, generator=gen, device="cuda") * 0.01 for n in ns]
+    plain = grads[-1].clone()
+    rng = np.random.default_rng(6)
+    # large values in blocks of 64, about as many as k: the sample's runs meet
+    # too many of them in some draws
+    misled = torch_dev(_awkward("blocks", ns[-1], rng).astype(np.float32))
+    resids = [torch.zeros(n, device="cuda") for n in ns]
+    out = B.alloc_payload("topk_sampled", 0.01, ns)
+    ws = B.alloc_workspace("topk_sampled", 0.01, ns, 1)
+    call = B.CompressCall("topk_sampled", 0.01, grads, resids, out, ws)
+
+    def one(seed, tail):
+        grads[-1].copy_(tail)
+        for e in resids:
+            e.zero_()
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        torch.cuda.synchronize()
+        a.record()
+        call(seed)
+        b.record()
+        b.synchronize()
+        return a.elapsed_time(b), B.bytecomp_topk_stats("topk_sampled", 0.01, ns, ws)[1]
+
+    seed = next((s for s in range(300) if one(s, misled)[1] == 1), None)
+    assert seed is not None, "no draw of the sample misleads"
+    with_fb = [one(seed, misled) for _ in range(9)]
+    without = [one(seed, plain) for _ in range(9)]
+    assert all(fb == 1 for _, fb in with_fb) and all(fb == 0 for _, fb in without)
+    slow, fast = (sorted(t for t, _ in x)[4] for x in (with_fb, without))
+    assert slow < fast + 0.5, (slow, fast)
