@@ -386,9 +386,8 @@ int bytecomp_device_status(void* ws, size_t ws_bytes, void* stream, uint32_t* fl
  *               fallback the bin of the k-th key, in short tensors of the
  *               sampled kind its key to 2^-13); at least the sum of
  *               the k_t, at most the sum of the n_t
- *   fallbacks   tensors whose sample misled (fewer than k_t candidates
- *               above its threshold, or the k-th key beyond the range it
- *               promised), so that they took the exact histogram path
+ *   fallbacks   tensors whose sampled threshold left fewer than k_t
+ *               candidates, so that they took the exact histogram path
  *               (0 for BC_TOPK and on the few-chunk path)
  * For monitoring and tuning (DGC's sampling); results never depend on it.
  * BC_E_KIND for other kinds, BC_E_WORKSPACE when ws is smaller than the

@@ -957,7 +957,7 @@ int bytecomp_topk_stats(int kind, double ratio, const uint64_t* n, int T, const 
     uint32_t nfb = 0;
     // the few-chunk path keeps another per-tensor value in t_fb
     if (kind == BC_TOPK_SAMPLED && C > topk_few_chunks_limit())
-        for (uint32_t x : fb) nfb += x != 0u;
+        for (uint32_t x : fb) nfb += x & 1u;  // kFbFew
     *candidates = cand;
     *fallbacks = nfb;
     return BC_OK;

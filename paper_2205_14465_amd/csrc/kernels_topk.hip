@@ -56,14 +56,17 @@ namespace bc {
 namespace {
 
 // A tensor's threshold word (t_thr): the threshold key, whose low 10 bits
-// are zero, with the shift s of the candidates' bins in bits 3..0.  t_zero
+// are zero, with the shift s of the candidates' bins in bits 4..0.  t_zero
 // holds the key from which the stream pass writes e_new = +0.0 at once
 // (kNoEarlyZero: nowhere).
 constexpr uint32_t kNoEarlyZero = 0xFFFFFFFFu;
 constexpr uint32_t kExactShift = 10;  // bins of 2^10 keys: bits 30..20 of an exact threshold in 1024 of them
 __device__ __forceinline__ uint32_t thr_key(uint32_t w) { return w & ~0x3FFu; }
-__device__ __forceinline__ uint32_t thr_shift(uint32_t w) { return w & 15u; }
-// Bin of a candidate's key: the last bin takes everything past the range.
+__device__ __forceinline__ uint32_t thr_shift(uint32_t w) { return w & 31u; }
+// Whether a listed key is at or above the threshold (a tensor that find_bin
+// gave a higher threshold keeps its list), and the bin of one that is: the
+// last bin takes everything past the range.
+__device__ __forceinline__ bool cand_in(uint32_t key, uint32_t w) { return key >= thr_key(w); }
 __device__ __forceinline__ uint32_t cand_bin(uint32_t key, uint32_t w) {
     const uint32_t b = (key - thr_key(w)) >> thr_shift(w);
     return b < (uint32_t)kBins0 ? b : (uint32_t)kBins0 - 1u;
@@ -83,6 +86,12 @@ constexpr uint32_t kListMax = 512;  // candidates of a chunk listed in LDS at a 
 __device__ __forceinline__ float* cand_vel(const Ws& ws, uint32_t c, uint32_t r) {
     return (float*)(ws.t_cand + (size_t)c * kChunk + kChunk / 2) + ((r + 64u * c) & (kChunk / 2 - 1u));
 }
+
+// A tensor's fallback word (t_fb): what find_bin could not settle, and
+// whether its new threshold is there.
+constexpr uint32_t kFbFew = 1;   // fewer than k candidates: the whole tensor again
+constexpr uint32_t kFbPast = 2;  // the k-th past the bins' range: the candidates again
+constexpr uint32_t kFbReady = 4;
 
 constexpr uint32_t kWholeBelow = 4u * kChunk;  // shorter tensors are read whole, not sampled
 
@@ -355,15 +364,16 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
     // the threshold's place among the keys, and a place that the k-th key
     // hardly ever lies above: the k rule on the sample's size with margins
     uint32_t target = td.k, early = 0;
+    uint32_t ks = 0;
     if (!whole) {
         const uint64_t ppm = (uint64_t)llround(ratio * 1e6);
-        uint64_t ks = ((uint64_t)total * ppm + 999999u) / 1000000u;
+        ks = (uint32_t)(((uint64_t)total * ppm + 999999u) / 1000000u);
         if (ks < 1) ks = 1;
-        const uint64_t tg2 = ks + ks / 4 + 16;
-        target = (uint32_t)(tg2 < total ? tg2 : total);
+        const uint32_t tg2 = ks + ks / 4 + 16;
+        target = tg2 < total ? tg2 : total;
         // no early zeros where the whole sample falls short of the margin: the
         // exact path, which all but certainly follows, would put them back
-        early = tg2 < total && ks - ks / 4 > 8 ? (uint32_t)(ks - ks / 4 - 8) : 0u;
+        early = tg2 < total && ks - ks / 4 > 8 ? ks - ks / 4 - 8 : 0u;
     }
     {
         // thread i owns bins 2047 - 2i and 2046 - 2i
@@ -421,7 +431,11 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
-    const uint32_t thr = b0 << 20 | found[0] << 10;
+    uint32_t thr = b0 << 20 | found[0] << 10;
+    // fewer non-zeros in the sample than its margin asks for, but its k: only
+    // zeros stay out (with threshold 0 every element becomes a candidate: 16
+    // tensors of 1 M elements with 1.15 k non-zeros 276 us, 110 so)
+    if (!whole && thr == 0u && total - nz >= ks) thr = 1024u;
     uint32_t zero = kNoEarlyZero, span;
     if (whole) {  // every key past the k-th's 2^10 wins
         zero = thr + 1024u;
@@ -488,8 +502,10 @@ __device__ __forceinline__ void take_bins(uint32_t* gh, int hi, int copies, uint
 
 // The exact candidate threshold of a tensor, the bin of the k-th key in its
 // histogram of key bits 30..20, by a whole workgroup.
+// keep_zero: of the tensor's candidates, whose early zeros stay as they are.
 template <bool kInPass>
-__device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh) {
+__device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh,
+                                         bool keep_zero) {
     const int hi = kBins0 - threadIdx.x * 8;  // thread i owns the i-th eight bins from the top
     uint32_t h[8];
     take_bins<kInPass>(ws.t_hist + (size_t)t * copies * kBins0, hi, copies, h);
@@ -504,7 +520,7 @@ __device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, con
             const uint32_t thr = (uint32_t)(hi - 1 - q) << 20 | kExactShift;
             if constexpr (kInPass) {
                 put_agent(ws.t_thr + t, thr);
-                put_agent(ws.t_zero + t, kNoEarlyZero);
+                if (!keep_zero) put_agent(ws.t_zero + t, kNoEarlyZero);
             } else {
                 ws.t_thr[t] = thr;
                 ws.t_zero[t] = kNoEarlyZero;  // e_new is already written
@@ -514,10 +530,10 @@ __device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, con
     }
 }
 
-// The bin of the k-th candidate of a tensor, by a whole workgroup.  False:
-// fewer than k candidates, or the k-th in the last bin (which has no upper
-// edge); an exact threshold meets neither.
-__device__ __forceinline__ bool find_bin(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh,
+// The bin of the k-th candidate of a tensor, by a whole workgroup; otherwise
+// kFbFew, or kFbPast for the k-th in the last bin (which has no upper edge).
+// An exact threshold meets neither.
+__device__ __forceinline__ uint32_t find_bin(const TDesc& td, int t, int copies, const Ws& ws, uint64_t* sh,
                                          uint32_t* found) {
     const int hi = kBins0 - threadIdx.x * 8;
     uint32_t h[8];
@@ -537,18 +553,18 @@ __device__ __forceinline__ bool find_bin(const TDesc& td, int t, int copies, con
         above += h[q];
     }
     __syncthreads();
-    if (found[0] == (uint32_t)kBins0 - 1u) return false;  // total < k included
+    if (found[0] == (uint32_t)kBins0 - 1u) return total < td.k ? kFbFew : kFbPast;
     if (threadIdx.x == 0) {
         ws.t_prefix[t] = found[0];
         ws.t_krem[t] = td.k - found[1];
     }
-    return true;
+    return 0u;
 }
 
 __global__ __launch_bounds__(kBlock) void topk_find_thr(const TDesc* __restrict__ d, int copies, Ws ws) {
     __shared__ uint64_t sh[4];
     const TDesc td = d[blockIdx.x];
-    if (td.k) find_thr<false>(td, (int)blockIdx.x, copies, ws, sh);
+    if (td.k) find_thr<false>(td, (int)blockIdx.x, copies, ws, sh, false);
 }
 
 __global__ __launch_bounds__(kBlock) void topk_find_bin(const TDesc* __restrict__ d, int copies, Ws ws) {
@@ -557,10 +573,10 @@ __global__ __launch_bounds__(kBlock) void topk_find_bin(const TDesc* __restrict_
     const int t = blockIdx.x;
     const TDesc td = d[t];
     if (td.k == 0) return;
-    const bool ok = find_bin(td, t, copies, ws, sh, found);
+    const uint32_t fb = find_bin(td, t, copies, ws, sh, found);
     if (threadIdx.x != 0) return;
-    ws.t_fb[t] = ok ? 0u : 1u;  // bytecomp_topk_stats counts them
-    if (ok) return;
+    ws.t_fb[t] = fb;  // bytecomp_topk_stats counts kFbFew
+    if (fb == 0u) return;
     // one entry of the fallback's list: the tensor, and how many chunks the
     // entries before it have (t_krem and t_prefix count its finished chunks)
     ws.t_krem[t] = ws.t_prefix[t] = 0u;
@@ -710,9 +726,13 @@ __global__ __launch_bounds__(kBlock) void topk_compact(
     compact_chunk<kNT, kDGC, kStream>(td, t, blockIdx.x, copies, ws, f, l, list_u);
 }
 
-// The exact path for the tensors that find_bin listed, in one launch that
-// ends at once when there are none (the usual case).  Only the listed tensors'
-// chunks are visited.  Workgroups claim batches of consecutive ones, first
+// The tensors that find_bin listed, in one launch that ends at once when there
+// are none (the usual case).  kFbFew: the exact path over the whole tensor.
+// kFbPast (most values zero and k near the number of the others, or values
+// over many octaves between the sample's threshold and the k-th): the k-th is
+// among the candidates, so the two passes go over those and only give them a
+// threshold, the k-th's bits 30..20, whose bins reach; list and early zeros
+// stay.  Only the listed tensors' chunks are visited.  Workgroups claim batches of consecutive ones, first
 // all batches of the first pass, then all of the second: in the first the
 // chunks get back what the stream pass zeroed early and add their keys to
 // their tensor's histogram of bits 30..20, and whoever finishes a tensor's
@@ -724,6 +744,36 @@ __global__ __launch_bounds__(kBlock) void topk_compact(
 // and what other workgroups read goes out by put_agent (one listed tensor of
 // BERT-base cost 3.3 ms when all chunks of the call were visited one by one
 // with a release each).
+namespace {
+
+constexpr uint32_t kAllBins = 20;  // a threshold word that bins keys by their bits 30..20
+
+// Histogram of the candidates of chunks [c0, c1) in the bins of threshold
+// word w, a wave per chunk at a time.
+__device__ __forceinline__ void rebin_chunks(const Ws& ws, uint32_t c0, uint32_t c1, uint32_t w, uint32_t* lh) {
+    constexpr uint32_t kU = 8;  // a lane's loads in flight together
+    uint32_t zeros = 0;         // counted apart: they would all meet in one bin
+    for (uint32_t c = c0 + (uint32_t)wave_id(); c < c1; c += kBlock / 64) {
+        const uint32_t m = ws.t_ccount[c];
+        const uint2* cand = ws.t_cand + (size_t)c * kChunk;
+        for (uint32_t i0 = (uint32_t)lane_id(); i0 < m; i0 += 64 * kU) {
+            uint32_t key[kU];
+#pragma unroll
+            for (uint32_t u = 0; u < kU; ++u)
+                key[u] = i0 + 64 * u < m ? cand[cand_at(c, m, i0 + 64 * u)].y & 0x7FFFFFFFu : kNoKey;
+#pragma unroll
+            for (uint32_t u = 0; u < kU; ++u) {
+                if (key[u] == kNoKey || !cand_in(key[u], w)) continue;
+                if (key[u] == 0u) ++zeros;
+                else atomicAdd(&lh[cand_bin(key[u], w)], 1u);
+            }
+        }
+    }
+    if (zeros) atomicAdd(&lh[0], zeros);
+}
+
+}  // namespace
+
 template <bool kDGC>
 __global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict__ d, int copies, Ws ws) {
     __shared__ CompactLds l;
@@ -754,7 +804,21 @@ __global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict_
             const uint32_t j0 = f - (uint32_t)ws.t_off[i];
             const uint32_t j1 = j0 + (f1 - f) < td.nchunks ? j0 + (f1 - f) : td.nchunks;
             f += j1 - j0;
-            if (!second) {
+            if (second) {
+                if (threadIdx.x == 0)
+                    while (!(__hip_atomic_load(ws.t_fb + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kFbReady))
+                        __builtin_amdgcn_s_sleep(8);
+                __syncthreads();
+                acquire_agent();  // threshold and restored values written elsewhere
+            }
+            const bool past = ws.t_fb[t] & kFbPast;
+            if (past) {
+                for (int b = threadIdx.x; b < kBins0; b += kBlock) l.lh[b] = 0;
+                __syncthreads();
+                rebin_chunks(ws, td.chunk0 + j0, td.chunk0 + j1, second ? ws.t_thr[t] : kAllBins, l.lh);
+                __syncthreads();
+                flush_hist(l.lh, ws.t_hist + ((size_t)t * copies + f % (uint32_t)copies) * kBins0, kBins0);
+            } else if (!second) {
                 for (int b = threadIdx.x; b < kBins0; b += kBlock) l.lh[b] = 0;
                 const uint32_t zero = ws.t_zero[t];
                 for (uint32_t c = td.chunk0 + j0; c < td.chunk0 + j1; ++c) {
@@ -788,11 +852,6 @@ __global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict_
                 __syncthreads();
                 flush_hist(l.lh, ws.t_hist + ((size_t)t * copies + f % (uint32_t)copies) * kBins0, kBins0);
             } else {
-                if (threadIdx.x == 0)
-                    while (__hip_atomic_load(ws.t_fb + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 2u)
-                        __builtin_amdgcn_s_sleep(8);
-                __syncthreads();
-                acquire_agent();  // threshold and restored values written elsewhere
                 for (uint32_t c = td.chunk0 + j0; c < td.chunk0 + j1; ++c) {
                     compact_chunk<false, false, false>(td, t, c, copies, ws, none, l, nullptr);
                     __syncthreads();  // the next one clears the histogram
@@ -807,10 +866,10 @@ __global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict_
             if (second) {
                 (void)find_bin(td, t, copies, ws, l.sh, found);
             } else {
-                find_thr<true>(td, t, copies, ws, l.sh);
+                find_thr<true>(td, t, copies, ws, l.sh, past);
                 stores_done();
                 __syncthreads();
-                if (threadIdx.x == 0) put_agent(ws.t_fb + t, 2u);
+                if (threadIdx.x == 0) put_agent(ws.t_fb + t, (past ? kFbPast : kFbFew) | kFbReady);
             }
         }
     }
@@ -865,9 +924,10 @@ __global__ __launch_bounds__(kBlock) void topk_cand_count(const TDesc* __restric
         uint64_t lows = 0;
         for (uint32_t i0 = 0; i0 < m[u]; i0 += 64) {
             const uint32_t i = i0 + (uint32_t)lane;
-            const bool in = i < m[u];
+            bool in = i < m[u];
             uint32_t k = key[u];
             if (i0) k = in ? cand[cand_at(c, m[u], i)].y & 0x7FFFFFFFu : 0u;
+            in = in && cand_in(k, w[u]);
             const uint32_t b = cand_bin(k, w[u]);
             gt += (uint32_t)__popcll(__ballot(in && b > bin[u]));
             const bool inside = in && b == bin[u];
@@ -964,7 +1024,7 @@ __device__ __forceinline__ void recount_chunk(const Ws& ws, uint32_t c, uint32_t
         }
 #pragma unroll
         for (uint32_t q = 0; q < kU; ++q) {
-            const bool inside = i0 + 64 * q + (uint32_t)lane_id() < m && cand_bin(key[q], w) == bin;
+            const bool inside = i0 + 64 * q + (uint32_t)lane_id() < m && cand_in(key[q], w) && cand_bin(key[q], w) == bin;
             const uint32_t x = (key[q] - thr_key(w)) & low_mask;
             gt += (uint32_t)__popcll(__ballot(inside && x > tau_low));
             eq += (uint32_t)__popcll(__ballot(inside && x == tau_low));

@@ -37,7 +37,8 @@ struct Ws {
                             // after the histograms' copies, inside t_hist)
     uint32_t* t_prefix;     // [T] radix-select prefix, then the k-th key
     uint32_t* t_krem;       // [T] entries still to select
-    uint32_t* t_fb;         // [T] nonzero: the tensor takes the exact-histogram fallback (2: its threshold is found)
+    uint32_t* t_fb;         // [T] 1: the tensor takes the exact-histogram fallback, 2: its candidates are binned
+                            // again, + 4: the new threshold is found
     uint32_t* t_any;        // [kAnyWords] one 64-bit word, the tensors listed for the fallback (high half) and
                             // their chunks (low half), then its claims
     uint2* t_cand;          // [C * 4096] candidates (local index, value bits)

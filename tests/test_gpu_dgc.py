@@ -299,3 +299,45 @@ def test_topk_fallback_costs_its_tensor():
     assert all(fb == 1 for _, fb in with_fb) and all(fb == 0 for _, fb in without)
     slow, fast = (sorted(t for t, _ in x)[4] for x in (with_fb, without))
     assert slow < fast + 0.5, (slow, fast)
+
+
+@pytest.mark.parametrize("dgc", [False, True])
+@pytest.mark.parametrize("density", [0.0102, 0.0115, 0.0135, 0.016])
+def test_topk_few_more_nonzeros_than_k(density, dgc):
+    """Between k and about 1.25 k + margin non-zero values (the rows of an
+    embedding, an aggregate of two payloads): the k-th key lies far above
+    the threshold, and is found among the candidates; no tensor falls back
+    to the exact path.  Against the oracle bit for bit."""
+    import torch
+    from paper_2205_14465_amd import binding as B
+    rng = np.random.default_rng(int(density * 1e5))
+    ns = [250_003, 70_001, 16_384, 1_000_003]
+    ratio, m = 0.01, 0.9
+    grads = []
+    for n in ns:
+        x = np.zeros(n, np.float32)
+        at = rng.choice(n, size=int(np.ceil(n * density)), replace=False)
+        x[at] = rng.standard_normal(at.size) * np.exp(rng.standard_normal(at.size))
+        grads.append(x)
+    e = [np.zeros(n, np.float32) for n in ns]
+    u = [np.zeros(n, np.float32) for n in ns]
+    dg, de, du = [torch_dev(x) for x in grads], [torch_dev(x) for x in e], [torch_dev(x) for x in u]
+    out = B.alloc_payload("topk_sampled", ratio, ns)
+    ws = B.alloc_workspace("topk_sampled", ratio, ns, 1)
+    with topk_path("general"):
+        if dgc:
+            B.bytecomp_compress_dgc("topk_sampled", ratio, 3, m, dg, de, du, out, ws)
+            want, e, u = O.compress_dgc_set("topk_sampled", ratio, 3, m, grads, e, u)
+        else:
+            B.bytecomp_compress("topk_sampled", ratio, 3, dg, de, out, ws)
+            want, e = O.compress_set("topk_sampled", ratio, 3, grads, e)
+        torch.cuda.synchronize()
+        cand, fallbacks = B.bytecomp_topk_stats("topk_sampled", ratio, ns, ws)
+    assert fallbacks == 0
+    total = int(want["off"][-1])
+    assert np.array_equal(out["idx"].cpu().numpy().view(np.uint32)[:total], want["idx"])
+    assert np.array_equal(bits(out["val"].cpu().numpy()[:total]), bits(want["val"]))
+    for t in range(len(ns)):
+        assert np.array_equal(bits(de[t].cpu().numpy()), bits(e[t])), t
+        if dgc:
+            assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), t
