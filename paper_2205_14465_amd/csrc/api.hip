@@ -256,15 +256,11 @@ WsPlan plan_workspace(int kind, int T, uint64_t C, uint64_t sum_k, bool agg_tabl
             take(p.s_tab, t * 4096 * 4);
         }
     } else if (kind == BC_TOPK || kind == BC_TOPK_SAMPLED) {
-        // the general pipeline: copies of one histogram per tensor, then a
-        // word per tensor; the few-chunk path: up to 4 copies of digit 0, then
-        // digits 1 and 2
-        {
-            size_t per = T <= 256 ? 8 * (size_t)kBins0 : (size_t)topk_general_copies(T) * kBins0 + 1;
-            if (C <= kTopkFewChunksMax && per < 4 * kBins0 + 2 * kBins12) per = 4 * kBins0 + 2 * kBins12;
-            take(p.t_hist, t * per * 4);
-            p.t_zero = p.t_hist + t * (size_t)topk_general_copies(T) * kBins0 * 4;
-        }
+        // the general pipeline: copies of one histogram per tensor; the
+        // few-chunk path: up to 4 copies of digit 0, then digits 1 and 2
+        size_t per = (size_t)topk_general_copies(T) * kBins0;
+        if (C <= kTopkFewChunksMax && per < 4 * kBins0 + 2 * kBins12) per = 4 * kBins0 + 2 * kBins12;
+        take(p.t_hist, t * per * 4);
         take(p.t_thr, t * 4);
         take(p.t_prefix, t * 4);
         take(p.t_krem, t * 4);
@@ -309,7 +305,7 @@ Ws carve_workspace(void* base, const WsPlan& p) {
     w.q_max = (uint32_t*)at(p.q_max);
     w.q_slot = (uint32_t*)at(p.q_slot);
     w.t_hist = (uint32_t*)at(p.t_hist);
-    w.t_zero = (uint32_t*)at(p.t_zero);
+    w.t_zero = (uint32_t*)at(p.d_part);
     w.t_thr = (uint32_t*)at(p.t_thr);
     w.t_prefix = (uint32_t*)at(p.t_prefix);
     w.t_krem = (uint32_t*)at(p.t_krem);

@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
     uint32_t s = 4;
     while (s < max_shift && span > ((uint32_t)(kBins0 - 1) << s)) ++s;
     ws.t_thr[t] = thr | s;
-    ws.t_zero[t] = zero;
+    ws.t_zero[td.chunk0] = zero;
 }
 
 // Stores and a wait by which a workgroup hands data to others of the same
@@ -520,10 +520,10 @@ __device__ __forceinline__ void find_thr(const TDesc& td, int t, int copies, con
             const uint32_t thr = (uint32_t)(hi - 1 - q) << 20 | kExactShift;
             if constexpr (kInPass) {
                 put_agent(ws.t_thr + t, thr);
-                if (!keep_zero) put_agent(ws.t_zero + t, kNoEarlyZero);
+                if (!keep_zero) put_agent(ws.t_zero + td.chunk0, kNoEarlyZero);
             } else {
                 ws.t_thr[t] = thr;
-                ws.t_zero[t] = kNoEarlyZero;  // e_new is already written
+                ws.t_zero[td.chunk0] = kNoEarlyZero;  // e_new is already written
             }
         }
         above += h[q];
@@ -606,7 +606,7 @@ __device__ __forceinline__ void compact_chunk(const TDesc& td, int t, uint32_t c
     uint64_t* sh = l.sh;
     uint2* list = l.list;
     const uint32_t j = c - td.chunk0;
-    const uint32_t w = ws.t_thr[t], zero = ws.t_zero[t];
+    const uint32_t w = ws.t_thr[t], zero = ws.t_zero[td.chunk0];
     const uint32_t thr = thr_key(w);
     for (int b = threadIdx.x; b < kBins0; b += kBlock) lh[b] = 0;
     float v[kEpt], u[kEpt];
@@ -820,7 +820,7 @@ __global__ __launch_bounds__(kBlock) void topk_fallback(const TDesc* __restrict_
                 flush_hist(l.lh, ws.t_hist + ((size_t)t * copies + f % (uint32_t)copies) * kBins0, kBins0);
             } else if (!second) {
                 for (int b = threadIdx.x; b < kBins0; b += kBlock) l.lh[b] = 0;
-                const uint32_t zero = ws.t_zero[t];
+                const uint32_t zero = ws.t_zero[td.chunk0];
                 for (uint32_t c = td.chunk0 + j0; c < td.chunk0 + j1; ++c) {
                     const uint32_t m = ws.t_ccount[c];
                     if (td.resid && zero != kNoEarlyZero && (!kDGC || m <= kListMax)) {
@@ -1209,7 +1209,7 @@ __global__ __launch_bounds__(kBlock) void topk_emit(const TDesc* __restrict__ d,
         const uint64_t end = d[t].off + d[t].k;
         const uint32_t tau = ws.t_prefix[t];
         const uint64_t need = ws.t_krem[t];
-        const uint32_t zero = kDGC && m > kListMax ? kNoEarlyZero : ws.t_zero[t];
+        const uint32_t zero = kDGC && m > kListMax ? kNoEarlyZero : ws.t_zero[d[t].chunk0];
         const uint2* cand = ws.t_cand + (size_t)c * kChunk;
         uint64_t eq_seen = ws.t_eqb[c];
         uint64_t pos = ws.t_off[c];

@@ -31,10 +31,10 @@ struct Ws {
     uint32_t* q_slot;       // [C] one-pass compress: those bits | 1 << 31 once published, 0 otherwise
                             // (emptied before the kernel runs)
     // BC_TOPK, BC_TOPK_SAMPLED
-    uint32_t* t_hist;       // [T * 2048] histograms         
+    uint32_t* t_hist;       // [T * topk_general_copies(T) * 2048] histograms (few-chunk path: see there)
     uint32_t* t_thr;        // [T] candidate threshold (key; the general pipeline: with its bins' shift)
-    uint32_t* t_zero;       // [T] key from which the stream pass zeroes e_new at once (general pipeline;
-                            // after the histograms' copies, inside t_hist)
+    uint32_t* t_zero;       // [C] at a tensor's first chunk: the key from which the stream pass zeroes e_new at
+                            // once (general pipeline; d_part's room, free by then)
     uint32_t* t_prefix;     // [T] radix-select prefix, then the k-th key
     uint32_t* t_krem;       // [T] entries still to select
     uint32_t* t_fb;         // [T] 1: the tensor takes the exact-histogram fallback, 2: its candidates are binned
@@ -65,7 +65,7 @@ struct Ws {
 // size.  Regions a kind does not use have size 0.
 struct WsPlan {
     size_t flags, s_val, s_partial, s_info, s_tab, s_slot, q_max, q_slot;
-    size_t t_hist, t_zero, t_thr, t_prefix, t_krem, t_fb, t_any, t_cand, t_ccount, t_gt, t_eq, t_off, t_eqb;
+    size_t t_hist, t_thr, t_prefix, t_krem, t_fb, t_any, t_cand, t_ccount, t_gt, t_eq, t_off, t_eqb;
     size_t r_keys, r_tmp, r_ccount, r_coff, r_hist;
     size_t d_part, d_factor;
     size_t total;
@@ -123,11 +123,13 @@ constexpr uint32_t kAnyWords = 3;
 // Copies of each top-k histogram in the general pipeline for a call of T
 // tensors: workgroups add into copy (their index mod copies), which spreads
 // the atomic additions to the busiest bins; readers add the copies.
+// Many tensors do that by themselves, and their histograms are memory that
+// every call clears and reads (40000 tensors: 330 MB a copy).
 constexpr int kGeneralCopiesMax = 4;
-inline int topk_general_copies(int T) { return T <= 256 ? kGeneralCopiesMax : 2; }
+inline int topk_general_copies(int T) { return T <= 256 ? kGeneralCopiesMax : T <= 1024 ? 2 : 1; }
 // The copies' room later holds the histogram of the low s bits of the keys
 // in one candidate bin, so s is at most its logarithm (2048 words a copy).
-inline uint32_t topk_max_shift(int copies) { return copies == 4 ? 13u : 12u; }
+inline uint32_t topk_max_shift(int copies) { return copies == 4 ? 13u : copies == 2 ? 12u : 11u; }
 // A profiler range (roctx) around one C-ABI call: a push at construction,
 // the pop at scope exit; without a profiler attached both are plain calls.
 struct CallRange {

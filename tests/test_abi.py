@@ -177,6 +177,21 @@ def test_noalloc_compress_checks_before_any_device_work():
     assert L.bytecomp_compress_noalloc(0, 0.01, 0, t, 1, pay, None) == -9
 
 
+@pytest.mark.parametrize("T,copies", [(40, 4), (256, 4), (257, 2), (1024, 2), (1025, 1), (5000, 1)])
+def test_topk_workspace_holds_what_the_pipeline_uses(T, copies):
+    """Above the few-chunk limit a top-k workspace is the header, `copies`
+    histograms of 2048 words and four words per tensor, and per chunk its
+    candidate slot, 24 bytes of counts and 8 of partial sums, each array
+    rounded up to 256 bytes, and the fallback's words."""
+    n = 4096 * 60 if T < 1000 else 4096 * 3
+    chunks = T * (n // 4096)
+    assert chunks > 2048
+    room = T * (copies * 2048 * 4 + 16) + chunks * (4096 * 8 + 24 + 8)
+    for kind in ("topk", "topk_sampled"):
+        got = B.bytecomp_workspace_size(kind, 0.01, [n] * T, 1)
+        assert room <= got <= room + 16 * 256, (got, room)
+
+
 def test_workspace_size_grows_with_inputs():
     a = B.bytecomp_workspace_size("topk_sampled", 0.01, [1 << 20], 1)
     b = B.bytecomp_workspace_size("topk_sampled", 0.01, [1 << 21], 1)
