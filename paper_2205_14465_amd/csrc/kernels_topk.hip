@@ -200,12 +200,19 @@ __global__ __launch_bounds__(kBlock) void topk_hist_pass(const TDesc* __restrict
 // twice the time for a margin that the sample does not need.  Also clears the
 // tensor's histograms and, first of all kernels of a call, the fallback's
 // words.
-constexpr int kThrBlock = 1024;
-constexpr uint32_t kThrGroups = kWholeBelow / 4 / kThrBlock;  // groups of 4 elements a thread holds
+// Workgroups of 1024 threads (this kernel and topk_place); of 256 for calls
+// of more than 256 tensors, which fill the GPU by their number, and in which
+// a wide workgroup's barriers and idle waves are what short tensors wait for.
+// A call with 1024 against 256 threads: 16 tensors of 1 M elements 73 and
+// 80 us, BERT-base's 199 285 and 328, 300 of 100 thousand 114 and 110, 1000
+// of 9 thousand 103 and 77, 40000 of 400 2123 and 935 (with two histogram
+// copies in the first).
+constexpr int kWideBlock = 1024, kNarrowBlock = kBlock;
+constexpr int kWideTensors = 256;
 constexpr uint32_t kRun = 16;
 constexpr uint32_t kRunsMin = 4096 / kRun, kRunsMax = kWholeBelow / kRun;
 constexpr uint32_t kNoKey = 0xFFFFFFFFu;
-static_assert(kRunsMax <= 4 * kThrBlock && kWholeBelow / 4 / kRunsMin >= kRun / 4, "sampling geometry");
+static_assert(kRunsMax <= 4 * kNarrowBlock && kWholeBelow / 4 / kRunsMin >= kRun / 4, "sampling geometry");
 
 namespace {
 
@@ -257,8 +264,9 @@ __device__ __forceinline__ void group_keys(const TDesc& td, const TDesc& tg, con
     }
 }
 
-// Exclusive prefix over the 1024 threads; sh: one entry per wave, not used
-// by the scan before.
+// Exclusive prefix over the kThreads threads; sh: one entry per wave, not
+// used by the scan before.
+template <int kThreads>
 __device__ __forceinline__ uint32_t wide_scan(uint32_t x, uint32_t* sh) {
     const int lane = lane_id(), w = threadIdx.x >> 6;
     uint32_t inc = x;
@@ -271,25 +279,27 @@ __device__ __forceinline__ uint32_t wide_scan(uint32_t x, uint32_t* sh) {
     __syncthreads();
     uint32_t before = 0;
 #pragma unroll
-    for (int q = 0; q < kThrBlock / 64; ++q) before += q < w ? sh[q] : 0u;
+    for (int q = 0; q < kThreads / 64; ++q) before += q < w ? sh[q] : 0u;
     return before + inc - x;
 }
 
 }  // namespace
 
-template <bool kDGC>
-__global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restrict__ d, double ratio, uint64_t seed,
-                                                            int copies, uint32_t max_shift, Ws ws, DgcFuse f) {
-    __shared__ uint32_t lh[4 * kBins0];  // four copies of one histogram (lane mod 4), later of two with 1024 bins
+template <bool kDGC, int kThreads>
+__global__ __launch_bounds__(kThreads) void topk_threshold(const TDesc* __restrict__ d, double ratio, uint64_t seed,
+                                                           int copies, uint32_t max_shift, Ws ws, DgcFuse f) {
+    constexpr uint32_t kGroups = kWholeBelow / 4 / kThreads;  // groups of 4 elements a thread holds
+    constexpr uint32_t kLh = kThreads == kWideBlock ? 4 : 1;  // copies of a histogram (lane mod kLh)
+    __shared__ uint32_t lh[kLh * kBins0];  // of one, later of two with 1024 bins
     __shared__ uint32_t start[kRunsMax];  // first group of 4 of each run
-    __shared__ uint32_t sh[3][kThrBlock / 64];
+    __shared__ uint32_t sh[3][kThreads / 64];
     __shared__ uint32_t found[5];
     const int t = blockIdx.x;
     const TDesc td = d[t];
     if (t == 0 && threadIdx.x < kAnyWords) ws.t_any[threadIdx.x] = 0u;
     {
         u32x4* gh = (u32x4*)(ws.t_hist + (size_t)t * copies * kBins0);
-        for (int b = threadIdx.x; b < copies * kBins0 / 4; b += kThrBlock) gh[b] = u32x4{0u, 0u, 0u, 0u};
+        for (int b = threadIdx.x; b < copies * kBins0 / 4; b += kThreads) gh[b] = u32x4{0u, 0u, 0u, 0u};
     }
     if (td.k == 0) return;
     const TDesc tg = kDGC ? f.dg[t] : td;
@@ -312,20 +322,20 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
             }
         }
     }
-    for (int b = threadIdx.x; b < 4 * kBins0; b += kThrBlock) lh[b] = 0;
+    for (int b = threadIdx.x; b < (int)kLh * kBins0; b += kThreads) lh[b] = 0;
     if (threadIdx.x < 5) found[threadIdx.x] = 0u;
     __syncthreads();
     const uint32_t groups = whole ? units : runs * (kRun / 4);
     const uint32_t total = whole ? td.n : runs * kRun;
-    uint32_t key[4 * kThrGroups + 1];  // kNoKey: none
-    constexpr uint32_t kBatch = kDGC ? kThrGroups / 2 : kThrGroups;  // groups loaded together
+    uint32_t key[4 * kGroups + 1];  // kNoKey: none
+    constexpr uint32_t kBatch = kDGC ? 2 : 4;  // groups loaded together
 #pragma unroll
-    for (uint32_t q0 = 0; q0 < kThrGroups; q0 += kBatch) {
+    for (uint32_t q0 = 0; q0 < kGroups; q0 += kBatch) {
         uint32_t at[kBatch];
-        if (q0 * kThrBlock < groups) {  // places past the last group read it again
+        if (q0 * kThreads < groups) {  // places past the last group read it again
 #pragma unroll
             for (uint32_t q = 0; q < kBatch; ++q) {
-                uint32_t i = (q0 + q) * kThrBlock + threadIdx.x;
+                uint32_t i = (q0 + q) * kThreads + threadIdx.x;
                 i = i < groups ? i : groups - 1u;
                 at[q] = whole ? 4u * i : 4u * (start[i / 4] + i % 4);
             }
@@ -335,24 +345,25 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
         for (uint32_t q = 0; q < kBatch; ++q)
 #pragma unroll
             for (int p = 0; p < 4; ++p)
-                if ((q0 + q) * kThrBlock + threadIdx.x >= groups) key[4 * (q0 + q) + p] = kNoKey;
+                if ((q0 + q) * kThreads + threadIdx.x >= groups) key[4 * (q0 + q) + p] = kNoKey;
     }
-    key[4 * kThrGroups] = kNoKey;
+    key[4 * kGroups] = kNoKey;
     if (whole && threadIdx.x < td.n % 4) {  // past the last whole group
         const uint32_t i = 4u * units + threadIdx.x;
         const TDesc& src = kDGC ? tg : td;
         const float g = src.dtype == 0 ? gp((const float*)src.grad)[i] : h2f(gp((const uint16_t*)src.grad)[i]);
         const float u = kDGC ? gp((const float*)td.grad)[i] : 0.f;
         const float e = td.resid ? gp(td.resid)[i] : 0.f;
-        key[4 * kThrGroups] =
+        key[4 * kGroups] =
             key_of(form_v<kDGC>(g, u, e, td.resid != nullptr, f, kDGC && f.clip ? *f.clip : 1.f));
     }
     uint32_t zeros = 0;  // counted apart: they would all meet in one bin
-    uint32_t* mine = lh + (threadIdx.x & 3);
+    uint32_t* mine = lh + (threadIdx.x & (kLh - 1));
 #pragma unroll
-    for (uint32_t q = 0; q <= 4 * kThrGroups; ++q) {
+    for (uint32_t q = 0; q <= 4 * kGroups; ++q) {
+        if (q < 4 * kGroups && q / 4 * kThreads >= groups) continue;  // nobody's (uniform)
         if (key[q] == 0u) ++zeros;
-        else if (key[q] != kNoKey) atomicAdd(mine + 4u * (key[q] >> 20), 1u);
+        else if (key[q] != kNoKey) atomicAdd(mine + kLh * (key[q] >> 20), 1u);
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) zeros += (uint32_t)__shfl_xor((int)zeros, o, 64);
@@ -376,17 +387,20 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
         early = tg2 < total && ks - ks / 4 > 8 ? ks - ks / 4 - 8 : 0u;
     }
     {
-        // thread i owns bins 2047 - 2i and 2046 - 2i
-        const uint32_t top = (uint32_t)kBins0 - 1u - 2u * threadIdx.x;
-        uint32_t h[2] = {0, 0};
+        // thread i owns the i-th kPer bins from the top
+        constexpr uint32_t kPer = kBins0 / kThreads;
+        const uint32_t top = (uint32_t)kBins0 - 1u - kPer * threadIdx.x;
+        uint32_t h[kPer], sum = 0;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            h[0] += lh[4u * top + p];
-            h[1] += lh[4u * (top - 1u) + p];
+        for (uint32_t q = 0; q < kPer; ++q) {
+            h[q] = 0;
+#pragma unroll
+            for (uint32_t p = 0; p < kLh; ++p) h[q] += lh[kLh * (top - q) + p];
+            sum += h[q];
         }
-        uint32_t above = wide_scan(h[0] + h[1], sh[0]);
+        uint32_t above = wide_scan<kThreads>(sum, sh[0]);
 #pragma unroll
-        for (uint32_t q = 0; q < 2; ++q) {
+        for (uint32_t q = 0; q < kPer; ++q) {
             if (above < target && target <= above + h[q]) {
                 found[0] = top - q;
                 found[1] = above;
@@ -401,33 +415,44 @@ __global__ __launch_bounds__(kThrBlock) void topk_threshold(const TDesc* __restr
     }
     __syncthreads();
     const uint32_t b0 = found[0], above0 = found[1], b1 = found[2], above1 = found[3], nz = found[4];
-    for (int b = threadIdx.x; b < 4 * kBins0; b += kThrBlock) lh[b] = 0;
+    for (int b = threadIdx.x; b < (int)kLh * kBins0; b += kThreads) lh[b] = 0;
     __syncthreads();
 #pragma unroll
-    for (uint32_t q = 0; q <= 4 * kThrGroups; ++q) {
+    for (uint32_t q = 0; q <= 4 * kGroups; ++q) {
+        if (q < 4 * kGroups && q / 4 * kThreads >= groups) continue;
         if (key[q] == 0u) continue;
-        const uint32_t b = key[q] >> 20, x = 4u * (key[q] >> 10 & 1023u);
+        const uint32_t b = key[q] >> 20, x = kLh * (key[q] >> 10 & 1023u);
         if (b == b0) atomicAdd(mine + x, 1u);
-        if (early && b == b1) atomicAdd(mine + 4 * kBins12 + x, 1u);
+        if (early && b == b1) atomicAdd(mine + kLh * kBins12 + x, 1u);
     }
     if (threadIdx.x == 0 && nz) {
         if (b0 == 0) atomicAdd(lh, nz);
-        if (early && b1 == 0) atomicAdd(lh + 4 * kBins12, nz);
+        if (early && b1 == 0) atomicAdd(lh + kLh * kBins12, nz);
     }
     if (threadIdx.x < 4) found[threadIdx.x] = 0u;
     __syncthreads();
     {
-        const uint32_t bin = (uint32_t)kBins12 - 1u - threadIdx.x;
-        uint32_t h[2] = {0, 0};
+        constexpr uint32_t kPer = kBins12 / kThreads;
+        const uint32_t top = (uint32_t)kBins12 - 1u - kPer * threadIdx.x;
+        uint32_t h[2][kPer], sum[2] = {0, 0};
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-            h[0] += lh[4u * bin + p];
-            h[1] += lh[4u * (kBins12 + bin) + p];
+        for (uint32_t q = 0; q < kPer; ++q)
+#pragma unroll
+            for (uint32_t x = 0; x < 2; ++x) {
+                h[x][q] = 0;
+#pragma unroll
+                for (uint32_t p = 0; p < kLh; ++p) h[x][q] += lh[kLh * (x * kBins12 + top - q) + p];
+                sum[x] += h[x][q];
+            }
+        uint32_t a0 = above0 + wide_scan<kThreads>(sum[0], sh[1]);
+        uint32_t a1 = above1 + wide_scan<kThreads>(sum[1], sh[2]);
+#pragma unroll
+        for (uint32_t q = 0; q < kPer; ++q) {
+            if (a0 < target && target <= a0 + h[0][q]) found[0] = top - q;
+            if (early && a1 < early && early <= a1 + h[1][q]) found[1] = top - q;
+            a0 += h[0][q];
+            a1 += h[1][q];
         }
-        const uint32_t a0 = above0 + wide_scan(h[0], sh[1]);
-        const uint32_t a1 = above1 + wide_scan(h[1], sh[2]);
-        if (a0 < target && target <= a0 + h[0]) found[0] = bin;
-        if (early && a1 < early && early <= a1 + h[1]) found[1] = bin;
     }
     __syncthreads();
     if (threadIdx.x != 0) return;
@@ -973,7 +998,6 @@ __global__ __launch_bounds__(kBlock) void topk_cand_count(const TDesc* __restric
 // chunk its prefix.  Runs of up to kPlaceRegs chunks (tensors of up to
 // 1024 kPlaceRegs chunks) keep their counts in registers; longer runs are
 // gone through three times.
-constexpr int kPlaceBlock = kThrBlock;
 constexpr uint32_t kPlaceRegs = 8;
 
 namespace {
@@ -1045,14 +1069,15 @@ __device__ __forceinline__ uint32_t chunk_winners(uint32_t gt, uint32_t eq, uint
 
 }  // namespace
 
-__global__ __launch_bounds__(kPlaceBlock) void topk_place(const TDesc* __restrict__ d, int copies, Ws ws) {
-    __shared__ uint32_t sh[4][kPlaceBlock / 64];
+template <int kThreads>
+__global__ __launch_bounds__(kThreads) void topk_place(const TDesc* __restrict__ d, int copies, Ws ws) {
+    __shared__ uint32_t sh[3][kThreads / 64];
     __shared__ uint32_t found[2];
     const int t = blockIdx.x;
     const TDesc td = d[t];
     if (td.k == 0 || td.nchunks == 0) return;
     const uint32_t w = ws.t_thr[t], bin = ws.t_prefix[t], krem = ws.t_krem[t];
-    const uint32_t per = (td.nchunks + kPlaceBlock - 1) / kPlaceBlock;
+    const uint32_t per = (td.nchunks + kThreads - 1) / kThreads;
     const uint32_t lo = threadIdx.x * per;
     const uint32_t hi = lo + per < td.nchunks ? lo + per : td.nchunks;
     uint32_t* eqp = ws.t_eq + td.chunk0;
@@ -1071,13 +1096,13 @@ __global__ __launch_bounds__(kPlaceBlock) void topk_place(const TDesc* __restric
         }
     }
     // the krem-th largest of the low bits: thread i owns the i-th run of
-    // max(1, 2^s / 1024) bins from the top
-    const uint32_t bins = 1u << thr_shift(w), run = bins <= (uint32_t)kPlaceBlock ? 1u : bins / kPlaceBlock;
+    // max(1, 2^s / kThreads) bins from the top
+    const uint32_t bins = 1u << thr_shift(w), run = bins <= (uint32_t)kThreads ? 1u : bins / kThreads;
     const bool owns = threadIdx.x * run < bins;
     const uint32_t* gh = ws.t_hist + (size_t)t * copies * kBins0 + (owns ? bins - threadIdx.x * run : run);
     uint32_t mine = 0;
     for (uint32_t q = 1; owns && q <= run; ++q) mine += *(gh - q);
-    uint32_t above = wide_scan(mine, sh[0]);
+    uint32_t above = wide_scan<kThreads>(mine, sh[0]);
     if (owns && above < krem && krem <= above + mine) {
         uint32_t q = 1, x = *(gh - 1);
         while (krem > above + x) {
@@ -1152,7 +1177,7 @@ __global__ __launch_bounds__(kPlaceBlock) void topk_place(const TDesc* __restric
         }
     }
     // tau-equal candidates before each run, then winners before each run
-    const uint32_t eqb0 = wide_scan(eq_run, sh[1]);
+    const uint32_t eqb0 = wide_scan<kThreads>(eq_run, sh[1]);
     uint32_t sel_run = 0, e = eqb0;
     if (regs) {
 #pragma unroll
@@ -1168,7 +1193,7 @@ __global__ __launch_bounds__(kPlaceBlock) void topk_place(const TDesc* __restric
             e += x;
         }
     }
-    uint64_t pos = td.off + wide_scan(sel_run, sh[2]);
+    uint64_t pos = td.off + wide_scan<kThreads>(sel_run, sh[2]);
     e = eqb0;
     if (regs) {
 #pragma unroll
@@ -1617,8 +1642,12 @@ hipError_t launch_topk_t(int kind, double ratio, uint64_t seed, const TDesc* d, 
         (void)launch_timed(kTimedTopkCompact, topk_compact<false, false, false>, dim3(C), blk, 0, s, d, T, R, ws, none);
         hipLaunchKernelGGL(topk_find_bin, dim3(T), blk, 0, s, d, R, ws);
     } else {  // sampled threshold, exact fallback per tensor
-        hipLaunchKernelGGL(topk_threshold<kDGC>, dim3(T), dim3(kThrBlock), 0, s, d, ratio, seed, R,
-                           topk_max_shift(R), ws, f);
+        if (T > kWideTensors)
+            hipLaunchKernelGGL((topk_threshold<kDGC, kNarrowBlock>), dim3(T), dim3(kNarrowBlock), 0, s, d, ratio, seed,
+                               R, topk_max_shift(R), ws, f);
+        else
+            hipLaunchKernelGGL((topk_threshold<kDGC, kWideBlock>), dim3(T), dim3(kWideBlock), 0, s, d, ratio, seed, R,
+                               topk_max_shift(R), ws, f);
         if (C > kNtChunks)
             (void)launch_timed(kTimedTopkCompact, topk_compact<true, kDGC, true>, dim3(C), blk, 0, s, d, T, R, ws, f);
         else
@@ -1631,7 +1660,10 @@ hipError_t launch_topk_t(int kind, double ratio, uint64_t seed, const TDesc* d, 
         hipLaunchKernelGGL(topk_cand_count<4>, dim3((C + 15) / 16), blk, 0, s, d, T, C, R, ws);
     else
         hipLaunchKernelGGL(topk_cand_count<1>, dim3((C + 3) / 4), blk, 0, s, d, T, C, R, ws);
-    hipLaunchKernelGGL(topk_place, dim3(T), dim3(kPlaceBlock), 0, s, d, R, ws);
+    if (T > kWideTensors)
+        hipLaunchKernelGGL(topk_place<kNarrowBlock>, dim3(T), dim3(kNarrowBlock), 0, s, d, R, ws);
+    else
+        hipLaunchKernelGGL(topk_place<kWideBlock>, dim3(T), dim3(kWideBlock), 0, s, d, R, ws);
     hipLaunchKernelGGL(topk_emit<kDGC>, dim3((C + kBlock / 64 - 1) / (kBlock / 64)), blk, 0, s, d, T, C, idx, val,
                        ws);
     return hipGetLastError();

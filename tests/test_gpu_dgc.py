@@ -341,3 +341,45 @@ def test_topk_few_more_nonzeros_than_k(density, dgc):
         assert np.array_equal(bits(de[t].cpu().numpy()), bits(e[t])), t
         if dgc:
             assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), t
+
+
+@pytest.mark.parametrize("kind,dgc", [("topk", False), ("topk_sampled", False), ("topk_sampled", True)])
+@pytest.mark.parametrize("T", [257, 1024, 1025])
+def test_topk_general_many_tensors(kind, dgc, T):
+    """General pipeline, tensor counts where the histogram copies, the widest
+    bins and the workgroups change, against the oracle bit for bit: sizes
+    around the sampling limit, tiny and empty ones, values with ties, zeros
+    and long tails among them."""
+    import torch
+    from paper_2205_14465_amd import binding as B
+    rng = np.random.default_rng(T)
+    sizes = [0, 1, 3, 4, 5, 100, 1023, 4095, 4096, 4097, 9000, 16383, 16384, 16385, 30001]
+    cases = ["heavy_tail", "tight", "equal", "zeros", "blocks"]
+    ns = [sizes[t % len(sizes)] for t in range(T)]
+    grads = [(_awkward(cases[t // len(sizes) % 6], n, rng) if t // len(sizes) % 6 < 5 else rng.standard_normal(n))
+             for t, n in enumerate(ns)]
+    grads = [g.astype(np.float16 if not dgc and t % 7 == 2 and np.abs(g).max(initial=0) < 1e4 else np.float32)
+             for t, g in enumerate(grads)]
+    e = [np.zeros(n, np.float32) for n in ns]
+    u = [np.zeros(n, np.float32) for n in ns]
+    ratio, m, seed = 0.02, 0.9, 77
+    dg, de, du = [torch_dev(x) for x in grads], [torch_dev(x) for x in e], [torch_dev(x) for x in u]
+    out = B.alloc_payload(kind, ratio, ns)
+    ws = B.alloc_workspace(kind, ratio, ns, 1)
+    ws.fill_(0xA5)
+    B.bytecomp_workspace_init(ws)
+    with topk_path("general"):
+        if dgc:
+            B.bytecomp_compress_dgc(kind, ratio, seed, m, dg, de, du, out, ws)
+            want, e, u = O.compress_dgc_set(kind, ratio, seed, m, grads, e, u)
+        else:
+            B.bytecomp_compress(kind, ratio, seed, dg, de, out, ws)
+            want, e = O.compress_set(kind, ratio, seed, grads, e)
+    torch.cuda.synchronize()
+    total = int(want["off"][-1])
+    assert np.array_equal(out["idx"].cpu().numpy().view(np.uint32)[:total], want["idx"])
+    assert np.array_equal(bits(out["val"].cpu().numpy()[:total]), bits(want["val"]))
+    for t in range(T):
+        assert np.array_equal(bits(de[t].cpu().numpy()), bits(e[t])), t
+        if dgc:
+            assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), t
