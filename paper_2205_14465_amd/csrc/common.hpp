@@ -161,23 +161,30 @@ __device__ __forceinline__ bool whole_chunk(const TDesc& td, uint32_t j) {
 
 typedef f32x4 f32x4_any __attribute__((aligned(4)));
 typedef u32x2 u32x2_any __attribute__((aligned(2)));
-// Four consecutive elements from element i on, any i.
+// Four consecutive elements from element i of p on, any i.
 template <bool kNT = false>
-__device__ __forceinline__ f32x4 ldg4f_any(const float* p) {
-    if constexpr (kNT) return __builtin_nontemporal_load((const BC_GLOBAL f32x4_any*)p);
-    else return *(const BC_GLOBAL f32x4_any*)p;
+__device__ __forceinline__ f32x4 ldg4f_any(const float* p, uint32_t i) {
+    const BC_GLOBAL f32x4_any* at = (const BC_GLOBAL f32x4_any*)((const BC_GLOBAL char*)p + 4u * i);
+    if constexpr (kNT) return __builtin_nontemporal_load(at);
+    else return *at;
 }
 template <bool kNT = false>
-__device__ __forceinline__ u32x2 ldg4h_any(const uint16_t* p) {
-    if constexpr (kNT) return __builtin_nontemporal_load((const BC_GLOBAL u32x2_any*)p);
-    else return *(const BC_GLOBAL u32x2_any*)p;
+__device__ __forceinline__ u32x2 ldg4h_any(const uint16_t* p, uint32_t i) {
+    const BC_GLOBAL u32x2_any* at = (const BC_GLOBAL u32x2_any*)((const BC_GLOBAL char*)p + 2u * i);
+    if constexpr (kNT) return __builtin_nontemporal_load(at);
+    else return *at;
 }
 
-// First element that a thread's load of round r covers: its own group's, or
-// the fourth from the tensor's end (n >= 4).
+// A thread's load of round r of chunk j covers its own group of four, or the
+// tensor's last four elements (n >= 4): element load_base + load_at of the
+// tensor.  The base is uniform (the group before the chunk, where a last
+// chunk of fewer than four elements reaches back to) and the rest a small
+// 32-bit offset, so that the loads need no 64-bit addresses per thread.
+__device__ __forceinline__ size_t load_base(uint32_t j) { return j ? (size_t)j * kChunk - 4u : 0u; }
 __device__ __forceinline__ uint32_t load_at(uint32_t n, uint32_t j, int r) {
-    const uint32_t e = j * (uint32_t)kChunk + 1024u * r + 4u * threadIdx.x;
-    return e < n - 4u ? e : n - 4u;
+    const uint32_t e = (j ? 4u : 0u) + 1024u * r + 4u * threadIdx.x;
+    const uint32_t last = n - 4u - (uint32_t)load_base(j);
+    return e < last ? e : last;
 }
 
 // Which of a thread's elements exist in chunk j of a tensor of n elements.
@@ -222,6 +229,21 @@ __device__ __forceinline__ float g_elem(const f32x4& gf, const u32x2& gh, int q)
     else return h2f(((q < 2 ? gh.x : gh.y) >> (16 * (q & 1))) & 0xFFFFu);
 }
 
+// Elements 0, 1 and 2 of a tensor of fewer than four (the last again where
+// there are fewer: mend_tail keeps what exists, in thread 0).
+template <int DT>
+__device__ __forceinline__ float tiny_elem(const TDesc& td, uint32_t q, bool use_resid) {
+    const uint32_t i = q < td.n ? q : td.n - 1u;
+    const float g = DT == 0 ? gp((const float*)td.grad)[i] : h2f(gp((const uint16_t*)td.grad)[i]);
+    return use_resid ? g + gp(td.resid)[i] : g;
+}
+template <int DT>
+__device__ __forceinline__ void load_tiny(const TDesc& td, bool use_resid, float (&v)[kEpt]) {
+    v[0] = tiny_elem<DT>(td, 0, use_resid);
+    v[1] = tiny_elem<DT>(td, 1, use_resid);
+    v[2] = tiny_elem<DT>(td, 2, use_resid);
+}
+
 // Load the 16 elements a thread owns of chunk `j` of tensor `td`, forming
 // v = widen(g) + e (e = 0 when there is no residual or `use_resid` is
 // false).  Elements past the tensor's end read as +0.0 and are reported
@@ -235,13 +257,13 @@ __device__ __forceinline__ void load_chunk(const TDesc& td, uint32_t j, bool use
         u32x2 gh[kRounds];
 #pragma unroll
         for (int r = 0; r < kRounds; ++r) {
-            if constexpr (DT == 0) gf[r] = ldg4f_any<kNT>((const float*)td.grad + load_at(n, j, r));
-            else gh[r] = ldg4h_any<kNT>((const uint16_t*)td.grad + load_at(n, j, r));
+            if constexpr (DT == 0) gf[r] = ldg4f_any<kNT>((const float*)td.grad + load_base(j), load_at(n, j, r));
+            else gh[r] = ldg4h_any<kNT>((const uint16_t*)td.grad + load_base(j), load_at(n, j, r));
         }
         if (use_resid) {
             f32x4 ev[kRounds];
 #pragma unroll
-            for (int r = 0; r < kRounds; ++r) ev[r] = ldg4f_any<kNT>(td.resid + load_at(n, j, r));
+            for (int r = 0; r < kRounds; ++r) ev[r] = ldg4f_any<kNT>(td.resid + load_base(j), load_at(n, j, r));
 #pragma unroll
             for (int r = 0; r < kRounds; ++r)
 #pragma unroll
@@ -255,15 +277,7 @@ __device__ __forceinline__ void load_chunk(const TDesc& td, uint32_t j, bool use
     } else {
 #pragma unroll
         for (int i = 0; i < kEpt; ++i) v[i] = 0.f;
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (uint32_t q = 0; q < 3; ++q) {
-                if (q >= n) continue;
-                if (DT == 0) v[q] = gp((const float*)td.grad)[q];
-                else v[q] = h2f(gp((const uint16_t*)td.grad)[q]);
-                if (use_resid) v[q] = v[q] + gp(td.resid)[q];
-            }
-        }
+        load_tiny<DT>(td, use_resid, v);
     }
     valid = 0xFFFFu;
     if (!whole_chunk(td, j)) {
@@ -288,7 +302,6 @@ __device__ __forceinline__ void load_v(const TDesc& td, uint32_t j, bool use_res
 struct RawChunk {
     uint32_t g[kEpt];
     float e[kEpt];
-    uint32_t valid;
 };
 
 // The loads are non-temporal: the one-pass kernels, which use this, read
@@ -297,67 +310,62 @@ struct RawChunk {
 // occur (td.dtype decides).  A kernel that keeps loads in flight across
 // iterations is instantiated per kDT so that the common single-dtype calls
 // have one load sequence (no merge of two register sets that would make
-// the compiler wait for the loads).
+// the compiler wait for the loads).  For the same reason tensors of fewer
+// than four elements take it too, on their descriptor's first 16 bytes
+// (dsc: any descriptor of the call); raw_to_v reads their elements.
 template <int kDT>
-__device__ __forceinline__ void load_raw(const TDesc& td, uint32_t j, bool use_resid, RawChunk& r) {
+__device__ __forceinline__ void load_raw(const TDesc* dsc, const TDesc& td, uint32_t j, bool use_resid, RawChunk& r) {
     if constexpr (kDT == 2) {
-        if (td.dtype == 0) load_raw<0>(td, j, use_resid, r);
-        else load_raw<1>(td, j, use_resid, r);
+        if (td.dtype == 0) load_raw<0>(dsc, td, j, use_resid, r);
+        else load_raw<1>(dsc, td, j, use_resid, r);
     } else {
-        const uint32_t n = td.n;
-        r.valid = whole_chunk(td, j) ? 0xFFFFu : valid_of(n, j);
-        if (n >= 4u) {
+        const bool tiny = td.n < 4u;
+        const uint32_t n = tiny ? 4u : td.n;  // load_at: 0 for all
+        const void* g = tiny ? (const void*)dsc : td.grad;
+        const float* e = tiny ? (const float*)dsc : td.resid;
+#pragma unroll
+        for (int rr = 0; rr < kRounds; ++rr) {
+            if constexpr (kDT == 0) {
+                const f32x4 x = ldg4f_any<true>((const float*)g + load_base(j), load_at(n, j, rr));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) r.g[4 * rr + q] = f2u(x[q]);
+            } else {
+                const u32x2 h = ldg4h_any<true>((const uint16_t*)g + load_base(j), load_at(n, j, rr));
+                r.g[4 * rr] = h.x;
+                r.g[4 * rr + 1] = h.y;
+            }
+        }
+        if (use_resid) {
 #pragma unroll
             for (int rr = 0; rr < kRounds; ++rr) {
-                if constexpr (kDT == 0) {
-                    const f32x4 x = ldg4f_any<true>((const float*)td.grad + load_at(n, j, rr));
+                const f32x4 y = ldg4f_any<true>(e + load_base(j), load_at(n, j, rr));
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) r.g[4 * rr + q] = f2u(x[q]);
-                } else {
-                    const u32x2 h = ldg4h_any<true>((const uint16_t*)td.grad + load_at(n, j, rr));
-                    r.g[4 * rr] = h.x;
-                    r.g[4 * rr + 1] = h.y;
-                }
+                for (int q = 0; q < 4; ++q) r.e[4 * rr + q] = y[q];
             }
-            if (use_resid) {
-#pragma unroll
-                for (int rr = 0; rr < kRounds; ++rr) {
-                    const f32x4 y = ldg4f_any<true>(td.resid + load_at(n, j, rr));
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) r.e[4 * rr + q] = y[q];
-                }
-            }
-            return;
-        }
-        if (threadIdx.x != 0) return;  // the others have no elements
-#pragma unroll
-        for (uint32_t q = 0; q < 3; ++q) {
-            const uint32_t i = q < n ? q : 0u;
-            if constexpr (kDT == 0) {
-                r.g[q] = gp((const uint32_t*)td.grad)[i];
-            } else {
-                const uint32_t hb = (uint32_t)gp((const uint16_t*)td.grad)[i];
-                if (q == 1) r.g[0] |= hb << 16;
-                else r.g[q >> 1] = hb;
-            }
-            if (use_resid) r.e[q] = gp(td.resid)[i];
         }
     }
 }
 
 // v = widen(g) + e from a RawChunk (e = 0 without residual), exactly as
-// load_v forms it (whole: whole_chunk of it); elements past the tensor's end
-// read as +0.0.
+// load_v forms it; elements past the tensor's end read as +0.0.  Returns
+// which exist.
 template <int kDT>
-__device__ __forceinline__ void raw_to_v(const TDesc& td, bool whole, bool use_resid, const RawChunk& r,
-                                         float (&v)[kEpt]) {
+__device__ __forceinline__ uint32_t raw_to_v(const TDesc& td, uint32_t j, bool use_resid, const RawChunk& r,
+                                             float (&v)[kEpt]) {
     const bool f16 = kDT == 1 || (kDT == 2 && td.dtype != 0);
 #pragma unroll
     for (int i = 0; i < kEpt; ++i) {
         const float g = f16 ? h2f((r.g[(i & ~3) + ((i >> 1) & 1)] >> (16 * (i & 1))) & 0xFFFFu) : u2f(r.g[i]);
         v[i] = use_resid ? g + r.e[i] : g;
     }
-    if (!whole) mend_tail(td.n, r.valid, v);
+    if (whole_chunk(td, j)) return 0xFFFFu;
+    if (td.n < 4u) {
+        if (f16) load_tiny<1>(td, use_resid, v);
+        else load_tiny<0>(td, use_resid, v);
+    }
+    const uint32_t valid = valid_of(td.n, j);
+    mend_tail(td.n, valid, v);
+    return valid;
 }
 
 // Load v that an earlier pass already stored (the residual buffer holds v),

@@ -377,21 +377,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     TDesc td{};
     if (c < C) {
         td = d[tensor_of_chunk(d, T, c)];
-        load_raw<kDT>(td, c - td.chunk0, td.resid != nullptr, raw);
+        load_raw<kDT>(d, td, c - td.chunk0, td.resid != nullptr, raw);
     }
     for (;; c += gridDim.x) {
         const bool have = c < C;
         float v[kEpt];
         uint32_t j = 0;
         float m_now = 0.f;
+        uint32_t valid_now = 0;
         if (have) {
             const int t = tensor_of_chunk(d, T, c);
             j = c - td.chunk0;
-            raw_to_v<kDT>(td, whole_chunk(td, j), td.resid != nullptr, raw, v);
+            valid_now = raw_to_v<kDT>(td, j, td.resid != nullptr, raw, v);
             uint32_t mk = 0;
 #pragma unroll
             for (int i = 0; i < kEpt; ++i) {
-                const uint32_t k = ((raw.valid >> i) & 1u) ? key_of(v[i]) : 0u;
+                const uint32_t k = ((valid_now >> i) & 1u) ? key_of(v[i]) : 0u;
                 mk = k > mk ? k : mk;
             }
             mk = block_max_u32(mk, sh);
@@ -402,12 +403,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 __hip_atomic_store(ws.q_slot + c, mk | 0x80000000u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
-        const uint32_t valid_now = raw.valid;
         const uint32_t cn = c + gridDim.x;
         TDesc tdn{};
+        RawChunk rawn;  // of its own: without a next chunk nothing of this one is kept
         if (cn < C) {
             tdn = d[tensor_of_chunk(d, T, cn)];
-            load_raw<kDT>(tdn, cn - tdn.chunk0, tdn.resid != nullptr, raw);
+            load_raw<kDT>(d, tdn, cn - tdn.chunk0, tdn.resid != nullptr, rawn);
         }
         if (prev) {
             // the uniforms need no scale: their arithmetic runs while the
@@ -430,6 +431,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         jp = j;
         mp = m_now;
         td = tdn;
+        raw = rawn;
     }
 }
 

@@ -273,7 +273,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1
     TDesc td{};
     if (c < C) {
         td = d[tensor_of_chunk(d, T, c)];
-        load_raw<kDT>(td, c - td.chunk0, td.resid != nullptr, raw);
+        load_raw<kDT>(d, td, c - td.chunk0, td.resid != nullptr, raw);
     }
     for (;; c += gridDim.x) {
         const bool have = c < C;
@@ -283,7 +283,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1
         if (have) {
             const int t = tensor_of_chunk(d, T, c);
             j = c - td.chunk0;
-            raw_to_v<kDT>(td, whole_chunk(td, j), td.resid != nullptr, raw, v);
+            (void)raw_to_v<kDT>(td, j, td.resid != nullptr, raw, v);
             store_sign_words(v, bits + td.off + (uint64_t)j * kChunkWords, chunk_words(td, j));
             const double p = block_sum_f64(thread_abs_sum(v), sh);
             if (td.nchunks == 1) {
@@ -297,9 +297,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1
         // the next chunk's loads go out before this round's wait
         const uint32_t cn = c + gridDim.x;
         TDesc tdn{};
+        RawChunk rawn;  // of its own: without a next chunk nothing of this one is kept
         if (cn < C) {
             tdn = d[tensor_of_chunk(d, T, cn)];
-            load_raw<kDT>(tdn, cn - tdn.chunk0, tdn.resid != nullptr, raw);
+            load_raw<kDT>(d, tdn, cn - tdn.chunk0, tdn.resid != nullptr, rawn);
         }
         if (prev) {
             float s = sp;
@@ -317,6 +318,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1
         jp = j;
         sp = s_now;
         td = tdn;
+        raw = rawn;
     }
 }
 

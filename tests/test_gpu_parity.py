@@ -351,6 +351,25 @@ def _check_word_kind(kind, got, want, grads, resids, got_e, want_e):
 
 @pytest.mark.parametrize("kind", ["sign", "terngrad", "qsgd4", "qsgd8"])
 @pytest.mark.parametrize("ef", [True, False])
+@pytest.mark.parametrize("dtypes", ["f32", "f16", "mixed"])
+def test_one_pass_tiny_tensors_between_others(kind, ef, dtypes):
+    """Tensors of fewer than four elements, whose elements the one-pass
+    kernels read apart from the chunk loads, before, after and between
+    chunks of every other kind, in each load sequence (first chunk of a
+    workgroup and prefetched ones: 4000 chunks and more)."""
+    rng = np.random.default_rng(43)
+    ns = [(1, 2, 3, 4, 5, 4095, 4097, 0, 3, 1, 70, 8194)[t % 12] for t in range(4001)] + [2]
+    grads, resids = make_set(ns, rng)
+    for t, g in enumerate(grads):
+        if dtypes == "f16" or (dtypes == "mixed" and t % 3 == 1):
+            grads[t] = g.astype(np.float16)
+    got, got_e = gpu_compress(kind, 1.0, SEED, grads, resids if ef else None)
+    want, want_e = O.compress_set(kind, 1.0, SEED, grads, resids if ef else None)
+    _check_word_kind(kind, got, want, grads, resids if ef else None, got_e, want_e)
+
+
+@pytest.mark.parametrize("kind", ["sign", "terngrad", "qsgd4", "qsgd8"])
+@pytest.mark.parametrize("ef", [True, False])
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 def test_one_pass_waits_given_up_from_the_host_stay_exact(kind, ef, dtype):
     # a wait limit of 0 makes every wait of the one-pass kernels stop
