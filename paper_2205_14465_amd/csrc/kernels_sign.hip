@@ -17,11 +17,12 @@
 // run: pass 1 writes the
 // bits, the chunk partial sums and v (into e); pass 2 sums the partials of
 // its tensor in the same fixed order, re-reads v and writes the residual.
-// The one-pass kernel's accesses are non-temporal at every size: lists of 300
-// to 15000 chunks took between 3% more and 15% less than with cached ones
-// (5662 chunks: 57 against 55 us with one set of buffers in turn, 58 against
-// 68 with three; 14963 chunks: 138 against 162), ResNet-50's kernel 58
-// against 68 us (5.3 TB/s).
+// The one-pass kernel's accesses are non-temporal at every size.  Measured
+// against cached ones with the gradients written just before the call, as a
+// backward pass leaves them, everything else out of the caches: one tensor
+// of 4 M elements 27 and 28 us, ResNet-50 64 and 71 (halves), four tensors of
+// 4.9 M 56 and 62; and with nothing written in between, all still cached:
+// 22 and 21, 61 and 57, 51 and 52.
 // (An earlier one-pass form that waited for each chunk's own tensor before
 // moving on was slower than two passes: the workgroups of a tensor waited
 // for each other with nothing to overlap.)
@@ -257,8 +258,8 @@ __device__ __forceinline__ float onepass_scale(const TDesc& td, uint64_t* slot, 
 }
 }  // namespace
 
-template <int kDT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kDT == 1 ? 5 : 4))) void sign_onepass(const TDesc* __restrict__ d, int T, uint32_t C,
+template <int kDT, int kWaves>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))) void sign_onepass(const TDesc* __restrict__ d, int T, uint32_t C,
                                                        uint32_t* __restrict__ bits, float* __restrict__ scale_out,
                                                        Ws ws, uint32_t wait_ticks) {
     __shared__ double sh[4];
@@ -365,29 +366,29 @@ __global__ __launch_bounds__(kBlock) void sign_residual_update(const TDesc* __re
 
 // ------------------------------------------------------------- launchers
 namespace {
-// Workgroups of sign_onepass<kDT> resident at once on the whole GPU.
-template <int kDT>
+// Workgroups of sign_onepass<kDT, kWaves> resident at once on the whole GPU.
+template <int kDT, int kWaves>
 uint32_t onepass_capacity(int cus) {
     static int per_cu = -1;
     if (per_cu < 0) {
         int nb = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sign_onepass<kDT>, kBlock, 0) != hipSuccess) nb = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, sign_onepass<kDT, kWaves>, kBlock, 0) != hipSuccess) nb = 0;
         per_cu = nb;
     }
     return (uint32_t)per_cu * (uint32_t)(cus > 0 ? cus : 0);
 }
 
 // One pass when every tensor fits the resident grid; false otherwise.
-template <int kDT>
+template <int kDT, int kWaves>
 bool sign_onepass_launch(const TDesc* d, int T, uint32_t C, uint32_t max_chunks, bool any_empty, uint32_t* bits,
                          float* scale, const Ws& ws, int cus, hipStream_t s) {
-    const uint32_t cap = onepass_capacity<kDT>(cus);
+    const uint32_t cap = onepass_capacity<kDT, kWaves>(cus);
     if (C == 0 || cap == 0 || max_chunks > cap) return false;
     const uint32_t grid = C < cap ? C : cap;
     hipLaunchKernelGGL(sign_onepass_reset, dim3((C + 255) / 256 < 1024 ? (C + 255) / 256 : 1024), dim3(256), 0, s,
                        C, ws);
-    (void)launch_timed(kTimedSignOnepass, sign_onepass<kDT>, dim3(grid), dim3(kBlock), 0, s, d, T, C, bits, scale, ws,
-                       onepass_wait_ticks());
+    (void)launch_timed(kTimedSignOnepass, sign_onepass<kDT, kWaves>, dim3(grid), dim3(kBlock), 0, s, d, T, C, bits,
+                       scale, ws, onepass_wait_ticks());
     if (any_empty) hipLaunchKernelGGL(sign_empty_scales, dim3((T + 255) / 256), dim3(256), 0, s, d, T, scale);
     return true;
 }
@@ -397,9 +398,13 @@ hipError_t launch_sign_compress(const TDesc* d, int T, uint32_t C, uint32_t max_
                                 bool any_f16, bool any_f32, uint32_t* bits, float* scale, const Ws& ws, int cus,
                                 hipStream_t s) {
     if (T <= 0) return hipSuccess;
-    const bool one = any_f16 && any_f32 ? sign_onepass_launch<2>(d, T, C, max_chunks, any_empty, bits, scale, ws, cus, s)
-                     : any_f16          ? sign_onepass_launch<1>(d, T, C, max_chunks, any_empty, bits, scale, ws, cus, s)
-                                        : sign_onepass_launch<0>(d, T, C, max_chunks, any_empty, bits, scale, ws, cus, s);
+    // fp32 elements: four waves per SIMD take ResNet-50's list in 64 us, five
+    // in 66, but only five hold a tensor of 1025 to 1280 chunks (one of 1200
+    // with 20 of 74: 31 us, in two passes 46); halves have registers for five
+    auto launch = [&](auto one_pass) { return one_pass(d, T, C, max_chunks, any_empty, bits, scale, ws, cus, s); };
+    const bool one = any_f16 && any_f32 ? launch(sign_onepass_launch<2, 4>) || launch(sign_onepass_launch<2, 5>)
+                     : any_f16          ? launch(sign_onepass_launch<1, 5>)
+                                        : launch(sign_onepass_launch<0, 4>) || launch(sign_onepass_launch<0, 5>);
     if (one) return hipGetLastError();
     // past the cache size: stream g and e_old past the cache, keep v (re-read
     // by pass 2) in it, and stream e_new out

@@ -368,6 +368,34 @@ def test_one_pass_tiny_tensors_between_others(kind, ef, dtypes):
     _check_word_kind(kind, got, want, grads, resids if ef else None, got_e, want_e)
 
 
+@pytest.mark.parametrize("dtypes", ["f32", "f16", "mixed"])
+@pytest.mark.parametrize("per_cu,one_pass", [(4, True), (5, True), (6, False)])
+def test_sign_one_pass_holds_five_chunks_per_compute_unit(dtypes, per_cu, one_pass):
+    """A list with one tensor of up to five chunks per compute unit (5.24 M
+    elements on 256) is compressed in one pass, whatever the dtypes; a longer
+    one takes two.  All against the oracle."""
+    import torch
+    from paper_2205_14465_amd import binding as B
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    rng = np.random.default_rng(47)
+    ns = [per_cu * cus * 4096 - 5, 70001, 3, 4096 * 9]
+    grads, resids = make_set(ns, rng)
+    for t, g in enumerate(grads):
+        if dtypes == "f16" or (dtypes == "mixed" and t == 1):
+            grads[t] = g.astype(np.float16)
+    ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    for x in ev:
+        x.record()
+    B.bytecomp_time_next_launch("sign_onepass", *ev)
+    try:
+        got, got_e = gpu_compress("sign", 1.0, SEED, grads, resids)
+    finally:
+        ran = not B.bytecomp_time_next_launch(None, None, None)
+    assert ran == one_pass
+    want, want_e = O.compress_set("sign", 1.0, SEED, grads, resids)
+    assert_sign_close(got, want, grads, resids, got_e, want_e)
+
+
 @pytest.mark.parametrize("kind", ["sign", "terngrad", "qsgd4", "qsgd8"])
 @pytest.mark.parametrize("ef", [True, False])
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
