@@ -91,6 +91,17 @@ __device__ __forceinline__ int tensor_of_chunk(const TDesc* __restrict__ d, int 
     return (int)reinterpret_cast<const uint32_t*>(d + T)[c];
 }
 
+// The chunk that workgroup b of a second pass over `chunks` chunks takes: the
+// last ones first, whose v the first pass (in order) left in the last-level
+// cache, but in groups of eight that keep their order, as workgroups are dealt
+// to the eight compute dies in turn and a chunk's v may still be in the L2 of
+// the die that wrote it (a sign call of 6 M elements 28 us, 32 backwards one
+// by one).
+__device__ __forceinline__ uint32_t backward_chunk(uint32_t b, uint32_t chunks) {
+    const uint32_t groups = chunks / 8u;
+    return b / 8u < groups ? 8u * (groups - 1u - b / 8u) + b % 8u : b;
+}
+
 // Pointers read from descriptor tables are generic; viewing them in the
 // global address space lets the compiler use global (not flat) memory
 // instructions with scalar base addresses.

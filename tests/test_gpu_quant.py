@@ -13,7 +13,7 @@ import pytest
 
 import oracle as O
 from tests.exact_ref import same_f32_arrays
-from tests.helpers import assert_resid_equal, bits, gpu_aggregate, gpu_compress
+from tests.helpers import assert_resid_equal, assert_sign_close, bits, gpu_aggregate, gpu_compress
 
 pytestmark = pytest.mark.gpu
 
@@ -220,3 +220,20 @@ def test_quant_compress_long_and_short_tensors(kind, dtype):
     got, got_e = gpu_compress(kind, 1.0, SEED + 7, grads, resids)
     want, want_e = O.compress_set(kind, 1.0, SEED + 7, grads, resids)
     check(kind, got, got_e, want, want_e)
+
+
+@pytest.mark.parametrize("kind", ["sign"] + KINDS)
+@pytest.mark.parametrize("chunks", [1544, 1545, 1551])
+def test_two_pass_chunk_counts_around_eight(kind, chunks):
+    """The second pass walks the chunks backwards in groups of eight: whole
+    groups, and a remainder of one and of seven, in lists whose longest
+    tensor is too long for one pass (1500 chunks)."""
+    rng = np.random.default_rng(chunks)
+    ns = [1500 * 4096, 3, (chunks - 1501) * 4096 - 1]
+    grads, resids = make_set(ns, rng)
+    got, got_e = gpu_compress(kind, 1.0, SEED, grads, resids)
+    want, want_e = O.compress_set(kind, 1.0, SEED, grads, resids)
+    if kind == "sign":
+        assert_sign_close(got, want, grads, resids, got_e, want_e)
+    else:
+        check(kind, got, got_e, want, want_e)
