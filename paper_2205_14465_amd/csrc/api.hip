@@ -831,7 +831,7 @@ int bytecomp_pack_part(int kind, double ratio, const uint64_t* n, int T, bc_payl
         const uint64_t range = count_of(kind, b[j + 1] - b[j], ppm);  // words of the range (word kinds)
         out_words += range;
         if (range > max_words) max_words = range;
-        if (n[t]) expected += (uint64_t)((double)cnt * (double)(b[j + 1] - b[j]) / (double)n[t]);
+        if (sparse && n[t]) expected += (uint64_t)((double)cnt * (double)(b[j + 1] - b[j]) / (double)n[t]);
     }
     hipStream_t s = (hipStream_t)stream;
     int dev = 0;

@@ -159,12 +159,15 @@ __global__ __launch_bounds__(kBlock) void part_copy_sparse(const PDesc* __restri
 }
 
 // Sign and quantizers (`bits` per element): copy tensor t's range words
-// and its scale; part_off gets the (host-computed) word offsets.  The
-// workgroups of a column share a tensor in pieces of kPackWords words, eight
-// loads in flight per thread (one workgroup for BERT-base's embedding, 2.9 MB
-// of 8-bit codes, would run on alone long after the others).
+// and its scale; part_off gets the (host-computed) word offsets.  kLong (some
+// range is longer than kPackWords words): the workgroups of a column share a
+// tensor in pieces of as many, eight loads in flight per thread (one
+// workgroup for BERT-base's embedding, 2.9 MB of 8-bit codes, would run on
+// alone long after the others).  Otherwise no more loads than words: 4096
+// tensors of up to 2048 words 30 us, 38 with the piece loop.
 constexpr uint32_t kPackWords = 2048;
 
+template <bool kLong>
 __global__ __launch_bounds__(kBlock) void part_copy_words(const PDesc* __restrict__ p, int T, uint32_t bits,
                                                           const uint32_t* __restrict__ in_bits,
                                                           const float* __restrict__ in_scale,
@@ -176,20 +179,24 @@ __global__ __launch_bounds__(kBlock) void part_copy_words(const PDesc* __restric
         // bits per element: the range starts on a word (lo is a multiple of 32)
         const uint32_t nw = (uint32_t)(((uint64_t)(pd.hi - pd.lo) * bits + 31u) / 32u);
         const uint64_t src = pd.in_off + (uint64_t)pd.lo / 32u * bits;
-        for (uint64_t b = (uint64_t)blockIdx.y * kPackWords; b < nw; b += (uint64_t)gridDim.y * kPackWords) {
-            uint32_t x[kPackWords / kBlock];
+        if constexpr (kLong) {
+            for (uint64_t b = (uint64_t)blockIdx.y * kPackWords; b < nw; b += (uint64_t)gridDim.y * kPackWords) {
+                uint32_t x[kPackWords / kBlock];
 #pragma unroll
-            for (uint32_t r = 0; r < kPackWords / kBlock; ++r) {
-                const uint64_t i = b + r * (uint32_t)kBlock + threadIdx.x;
-                x[r] = gp(in_bits)[src + (i < nw ? i : b)];
-            }
+                for (uint32_t r = 0; r < kPackWords / kBlock; ++r) {
+                    const uint64_t i = b + r * (uint32_t)kBlock + threadIdx.x;
+                    x[r] = gp(in_bits)[src + (i < nw ? i : b)];
+                }
 #pragma unroll
-            for (uint32_t r = 0; r < kPackWords / kBlock; ++r) {
-                const uint64_t i = b + r * (uint32_t)kBlock + threadIdx.x;
-                if (i < nw) gp(out_bits)[pd.out_off + i] = x[r];
+                for (uint32_t r = 0; r < kPackWords / kBlock; ++r) {
+                    const uint64_t i = b + r * (uint32_t)kBlock + threadIdx.x;
+                    if (i < nw) gp(out_bits)[pd.out_off + i] = x[r];
+                }
             }
+        } else {
+            for (uint32_t i = threadIdx.x; i < nw; i += kBlock) out_bits[pd.out_off + i] = gp(in_bits)[src + i];
         }
-        if (blockIdx.y == 0 && threadIdx.x == 0) {
+        if ((!kLong || blockIdx.y == 0) && threadIdx.x == 0) {
             out_scale[t] = gp(in_scale)[t];
             part_off[t] = pd.out_off;
             if (t == 0) part_off[T] = total;
@@ -206,10 +213,13 @@ hipError_t launch_pack_part(int word_bits, const PDesc* p, int T, bc_payload_dev
         // pieces of the longest range, while the grid (mostly idle where the
         // other tensors are short) stays under 64 workgroups per compute unit
         uint64_t pieces = (max_words + kPackWords - 1) / kPackWords;
-        if (pieces < 1) pieces = 1;
         if (pieces > 64u * (uint64_t)cus / grid) pieces = 64u * (uint64_t)cus / grid;
-        hipLaunchKernelGGL(part_copy_words, dim3(grid, (uint32_t)pieces), dim3(kBlock), 0, s, p, T,
-                           (uint32_t)word_bits, in.bits, in.scale, out.bits, out.scale, part_off, words);
+        if (pieces > 1)
+            hipLaunchKernelGGL(part_copy_words<true>, dim3(grid, (uint32_t)pieces), dim3(kBlock), 0, s, p, T,
+                               (uint32_t)word_bits, in.bits, in.scale, out.bits, out.scale, part_off, words);
+        else
+            hipLaunchKernelGGL(part_copy_words<false>, dim3(grid), dim3(kBlock), 0, s, p, T, (uint32_t)word_bits,
+                               in.bits, in.scale, out.bits, out.scale, part_off, words);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(part_count, dim3((T + 3) / 4), dim3(kBlock), 0, s, p, T, in.idx, part_off);
