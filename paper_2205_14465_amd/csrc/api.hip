@@ -810,7 +810,8 @@ int bytecomp_pack_part(int kind, double ratio, const uint64_t* n, int T, bc_payl
     } catch (const std::bad_alloc&) {
         return BC_E_SIZE;
     }
-    uint64_t in_off = 0, out_words = 0, max_words = 0, expected = 0;
+    uint64_t in_off = 0, out_words = 0, max_words = 0;
+    double expected = 0;  // the part's entries if every tensor's were spread evenly
     for (int t = 0; t < T; ++t) {
         if (n[t] >= kMaxN) return BC_E_SIZE;
         const uint64_t* b = bounds + (size_t)t * (parts + 1);
@@ -831,7 +832,7 @@ int bytecomp_pack_part(int kind, double ratio, const uint64_t* n, int T, bc_payl
         const uint64_t range = count_of(kind, b[j + 1] - b[j], ppm);  // words of the range (word kinds)
         out_words += range;
         if (range > max_words) max_words = range;
-        if (sparse && n[t]) expected += (uint64_t)((double)cnt * (double)(b[j + 1] - b[j]) / (double)n[t]);
+        if (sparse && n[t]) expected += (double)cnt * (double)(b[j + 1] - b[j]) / (double)n[t];
     }
     hipStream_t s = (hipStream_t)stream;
     int dev = 0;
@@ -845,7 +846,7 @@ int bytecomp_pack_part(int kind, double ratio, const uint64_t* n, int T, bc_payl
     const bc_payload_dev din{in.idx, in.val, in.bits, in.scale};
     const bc_payload_dev dout{out.idx, out.val, out.bits, out.scale};
     e = launch_pack_part(sparse ? 0 : quant_bits(kind) ? quant_bits(kind) : 1, (const PDesc*)en->dev, T, din, dout,
-                         part_off, out_words, max_words, expected, di.cus, s);
+                         part_off, out_words, max_words, (uint64_t)expected, di.cus, s);
     cache_mark_used(en, s);
     return hip_status(e);
 }

@@ -56,7 +56,8 @@ __device__ __forceinline__ void wave_lower_bounds(const uint32_t* idx, uint32_t 
 
 }  // namespace
 
-// Sparse packing takes two launches.  part_count leaves in part_off[t] the
+// Sparse packing takes two launches (three for large parts, launch_pack_part).
+// part_count leaves in part_off[t] the
 // range's first entry of tensor t (high 32 bits) and its number of entries
 // (low 32 bits) and clears part_off[T]; part_copy_sparse turns the counts
 // into offsets in every workgroup, copies, and counts its finished
@@ -78,14 +79,111 @@ __global__ __launch_bounds__(kBlock) void part_count(const PDesc* __restrict__ p
     if (lane_id() == 0) part_off[t] = (uint64_t)at[0] << 32 | (uint64_t)(at[1] - at[0]);
 }
 
-// Each workgroup copies spans of 1024 packed positions, four per thread,
-// whose source each thread finds by itself: a search over the offsets of
-// 256 runs of tensors in LDS, then a walk along the run (one tensor up to
-// 256 tensors).  The grid follows the entries expected of the part, up to
-// two workgroups per compute unit: each reads every tensor's count and adds
-// to one counter (512 workgroups for 134 spans: 11 us, 135: 7 us).
+// Each workgroup copies spans of packed positions, whose sources every thread
+// finds by itself: a search over the offsets of 256 runs of tensors in LDS,
+// then a walk along the run (one tensor up to 256 tensors), from the thread's
+// position before if that lies in the run too.  The grid follows the entries
+// expected of the part: each workgroup reads every tensor's count and adds to
+// one counter (512 workgroups for 134 spans: 11 us, 135: 7 us).  Spans are 1024 positions, four per thread, or 4096 where
+// the part holds more than the grid covers so (entries crowded into one part,
+// high ratios: 5 M entries 55 us with the short spans).
 constexpr uint32_t kPackSpan = 1024;
 
+namespace {
+
+// Packed positions b0 .. b0 + kPer * kBlock - 1, as far as below total.
+template <uint32_t kPer>
+__device__ __forceinline__ void copy_span(const PDesc* __restrict__ p, uint32_t per, const uint32_t* in_idx,
+                                          const float* in_val, uint32_t* out_idx, float* out_val,
+                                          const uint64_t* part_off, const uint64_t* run_off, uint64_t b0,
+                                          uint64_t total) {
+    const uint64_t m = total - b0 < kPer * (uint64_t)kBlock ? total - b0 : kPer * (uint64_t)kBlock;
+    uint64_t src[kPer];
+    uint32_t lo[kPer], ix[kPer];
+    float va[kPer];
+    // the tensor of this thread's position (its word, and the positions of it
+    // that come before) and where its run of tensors ends
+    uint64_t end = 0, left = 0, w = 0, at = 0, prev = 0;
+    uint32_t t = 0, first = 0;
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r) {
+        const uint32_t i = r * (uint32_t)kBlock + threadIdx.x;
+        const uint64_t o = b0 + (i < m ? i : (uint32_t)m - 1u);  // past the end: a position to read, not written
+        bool moved = r == 0;
+        if (o >= end) {
+            uint32_t run = 0;  // the last run that starts at or before o
+#pragma unroll
+            for (uint32_t b = kBlock / 2; b >= 1; b >>= 1)
+                if (run_off[run + b] <= o) run += b;
+            end = run + 1u < (uint32_t)kBlock ? run_off[run + 1u] : total;
+            t = run * per;
+            left = o - run_off[run];
+            w = part_off[t];
+            moved = true;
+        } else {
+            left += o - prev;
+        }
+        while (left >= (uint32_t)w) {
+            left -= (uint32_t)w;
+            w = part_off[++t];
+            moved = true;
+        }
+        if (moved) {
+            at = p[t].in_off + (w >> 32);
+            first = p[t].lo;
+        }
+        src[r] = at + left;
+        lo[r] = first;
+        prev = o;
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r) {
+        ix[r] = gp(in_idx)[src[r]];
+        va[r] = gp(in_val)[src[r]];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kPer; ++r) {
+        const uint32_t i = r * (uint32_t)kBlock + threadIdx.x;
+        if (i < m) {
+            gp(out_idx)[b0 + i] = ix[r] - lo[r];
+            gp(out_val)[b0 + i] = va[r];
+        }
+    }
+}
+
+}  // namespace
+
+namespace {
+// This thread's run of tensors, and the entries before it and of the part,
+// from the counts in part_off.
+struct Run {
+    uint32_t per, t0, t1;
+    uint64_t before, total;
+};
+__device__ __forceinline__ Run scan_counts(int T, const uint64_t* part_off, uint64_t* sh) {
+    Run r;
+    r.per = ((uint32_t)T + kBlock - 1u) / (uint32_t)kBlock;
+    r.t0 = threadIdx.x * r.per < (uint32_t)T ? threadIdx.x * r.per : (uint32_t)T;
+    r.t1 = r.t0 + r.per < (uint32_t)T ? r.t0 + r.per : (uint32_t)T;
+    uint64_t mine = 0;
+    for (uint32_t t = r.t0; t < r.t1; ++t) mine += (uint32_t)part_off[t];
+    r.before = block_excl_scan_u64(mine, sh, r.total);
+    return r;
+}
+// Offsets over the counts.
+__device__ __forceinline__ void put_offsets(int T, const Run& r, uint64_t* part_off) {
+    uint64_t run = r.before;
+    for (uint32_t t = r.t0; t < r.t1; ++t) {
+        const uint32_t c = (uint32_t)part_off[t];
+        part_off[t] = run;
+        run += c;
+    }
+    if (threadIdx.x == 0) part_off[T] = r.total;
+}
+}  // namespace
+
+// kLarge: no counting of finished workgroups; part_offsets follows.
+template <bool kLarge>
 __global__ __launch_bounds__(kBlock) void part_copy_sparse(const PDesc* __restrict__ p, int T,
                                                            const uint32_t* __restrict__ in_idx,
                                                            const float* __restrict__ in_val,
@@ -94,51 +192,20 @@ __global__ __launch_bounds__(kBlock) void part_copy_sparse(const PDesc* __restri
     __shared__ uint64_t run_off[kBlock];
     __shared__ uint64_t sh[4];
     __shared__ int last_sh;
-    const uint32_t per = ((uint32_t)T + kBlock - 1u) / (uint32_t)kBlock;  // tensors of a run
-    const uint32_t t0 = threadIdx.x * per < (uint32_t)T ? threadIdx.x * per : (uint32_t)T;
-    const uint32_t t1 = t0 + per < (uint32_t)T ? t0 + per : (uint32_t)T;
-    uint64_t mine = 0;
-    for (uint32_t t = t0; t < t1; ++t) mine += (uint32_t)part_off[t];
-    uint64_t total;
-    const uint64_t before = block_excl_scan_u64(mine, sh, total);
-    run_off[threadIdx.x] = before;
+    const Run r = scan_counts(T, part_off, sh);
+    run_off[threadIdx.x] = r.before;
     __syncthreads();
-    for (uint64_t b0 = (uint64_t)blockIdx.x * kPackSpan; b0 < total; b0 += (uint64_t)gridDim.x * kPackSpan) {
-        uint64_t src[kPackSpan / kBlock];
-        uint32_t lo[kPackSpan / kBlock], ix[kPackSpan / kBlock];
-        float va[kPackSpan / kBlock];
-#pragma unroll
-        for (uint32_t r = 0; r < kPackSpan / kBlock; ++r) {
-            uint64_t o = b0 + r * (uint32_t)kBlock + threadIdx.x;
-            if (o >= total) o = total - 1;  // a position to read; not written
-            uint32_t run = 0;               // the last run that starts at or before o
-#pragma unroll
-            for (uint32_t b = kBlock / 2; b >= 1; b >>= 1)
-                if (run_off[run + b] <= o) run += b;
-            uint32_t t = run * per;
-            uint64_t left = o - run_off[run];
-            uint64_t w = part_off[t];
-            while (left >= (uint32_t)w) {
-                left -= (uint32_t)w;
-                w = part_off[++t];
-            }
-            src[r] = p[t].in_off + (w >> 32) + left;
-            lo[r] = p[t].lo;
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < kPackSpan / kBlock; ++r) {
-            ix[r] = gp(in_idx)[src[r]];
-            va[r] = gp(in_val)[src[r]];
-        }
-#pragma unroll
-        for (uint32_t r = 0; r < kPackSpan / kBlock; ++r) {
-            const uint64_t o = b0 + r * (uint32_t)kBlock + threadIdx.x;
-            if (o < total) {
-                gp(out_idx)[o] = ix[r] - lo[r];
-                gp(out_val)[o] = va[r];
-            }
-        }
+    if (r.total <= (uint64_t)gridDim.x * kPackSpan) {
+        const uint64_t b0 = (uint64_t)blockIdx.x * kPackSpan;
+        if (b0 < r.total)
+            copy_span<kPackSpan / kBlock>(p, r.per, in_idx, in_val, out_idx, out_val, part_off, run_off, b0, r.total);
+    } else {
+        const uint64_t step = (uint64_t)gridDim.x * 4 * kPackSpan;
+        for (uint64_t b0 = (uint64_t)blockIdx.x * 4 * kPackSpan; b0 < r.total; b0 += step)
+            copy_span<4 * kPackSpan / kBlock>(p, r.per, in_idx, in_val, out_idx, out_val, part_off, run_off, b0,
+                                              r.total);
     }
+    if (kLarge) return;
     // done with the counts; the last workgroup replaces them.  Only reads
     // come before this point that it could overtake, and the barrier waits
     // for their data, so the addition needs no release (which would write
@@ -148,14 +215,12 @@ __global__ __launch_bounds__(kBlock) void part_copy_sparse(const PDesc* __restri
         last_sh = __hip_atomic_fetch_add((unsigned long long*)part_off + T, 1ull, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT) == (unsigned long long)gridDim.x - 1ull;
     __syncthreads();
-    if (!last_sh) return;
-    uint64_t run = before;
-    for (uint32_t t = t0; t < t1; ++t) {
-        const uint32_t c = (uint32_t)part_off[t];
-        part_off[t] = run;
-        run += c;
-    }
-    if (threadIdx.x == 0) part_off[T] = total;
+    if (last_sh) put_offsets(T, r, part_off);
+}
+
+__global__ __launch_bounds__(kBlock) void part_offsets(int T, uint64_t* part_off) {
+    __shared__ uint64_t sh[4];
+    put_offsets(T, scan_counts(T, part_off, sh), part_off);
 }
 
 // Sign and quantizers (`bits` per element): copy tensor t's range words
@@ -223,10 +288,21 @@ hipError_t launch_pack_part(int word_bits, const PDesc* p, int T, bc_payload_dev
         return hipGetLastError();
     }
     hipLaunchKernelGGL(part_count, dim3((T + 3) / 4), dim3(kBlock), 0, s, p, T, in.idx, part_off);
+    // above one short span per compute unit (262 thousand entries) as many
+    // workgroups as long spans, and a third launch in place of their additions
+    // to one counter: 500 thousand entries 20 us, 22 with the counter, 5 M 30
+    // and 55; a BERT-base part's 137 thousand 16 with the counter
     uint64_t blocks = expected / kPackSpan + 1;
-    if (blocks > 2u * (uint64_t)cus) blocks = 2u * (uint64_t)cus;
-    hipLaunchKernelGGL(part_copy_sparse, dim3((uint32_t)blocks), dim3(kBlock), 0, s, p, T, in.idx, in.val, out.idx,
-                       out.val, part_off);
+    if (blocks <= (uint64_t)cus) {
+        hipLaunchKernelGGL(part_copy_sparse<false>, dim3((uint32_t)blocks), dim3(kBlock), 0, s, p, T, in.idx, in.val,
+                           out.idx, out.val, part_off);
+    } else {
+        blocks = expected / (4 * kPackSpan) + 1;
+        if (blocks > 16u * (uint64_t)cus) blocks = 16u * (uint64_t)cus;
+        hipLaunchKernelGGL(part_copy_sparse<true>, dim3((uint32_t)blocks), dim3(kBlock), 0, s, p, T, in.idx, in.val,
+                           out.idx, out.val, part_off);
+        hipLaunchKernelGGL(part_offsets, dim3(1), dim3(kBlock), 0, s, T, part_off);
+    }
     return hipGetLastError();
 }
 

@@ -74,12 +74,13 @@ def test_pack_part_matches_oracle(kind, empty_part):
             assert np.array_equal(bits(out["val"].cpu().numpy()[:tot]), bits(want["val"])), j
 
 
-@pytest.mark.parametrize("case", ["runs", "skewed", "long_words", "short_words"])
+@pytest.mark.parametrize("case", ["runs", "skewed", "long_words", "short_words", "large", "many_tensors"])
 def test_pack_part_shapes(case):
     """Tensor counts past one per thread (runs of tensors, empty ones among
     them), a part that holds far more entries than its share of the range (the
-    copy's grid walks several spans per workgroup), and word ranges of several
-    pieces with a remainder and of less than one."""
+    copy's grid walks several spans per workgroup), word ranges of several
+    pieces with a remainder and of less than one, a part of more entries than
+    two spans per compute unit, and more tensors than entries of a part."""
     rng = np.random.default_rng(77)
     kind, ratio = "topk", 0.3
     if case == "runs":
@@ -88,6 +89,12 @@ def test_pack_part_shapes(case):
     elif case == "skewed":
         ns = [65, 300001, 7]
         grads = [(rng.standard_normal(n) * np.where(np.arange(n) < n * 0.35, 1.0, 1e-6)).astype(np.float32) for n in ns]
+    elif case == "large":
+        ns, ratio = [2_000_003, 70, 1_500_001], 0.9
+        grads = [(rng.standard_normal(n) * 0.01).astype(np.float32) for n in ns]
+    elif case == "many_tensors":
+        ns, ratio = [int(x) for x in rng.integers(0, 70, size=9000)], 0.01
+        grads = [(rng.standard_normal(n) * 0.01).astype(np.float32) for n in ns]
     else:
         kind = "qsgd8"
         ns = [1, 3 * 4 * 2048 * 4 + 33, 0, 4095, 8192] if case == "long_words" else [1, 3 * 4 * 2048, 0, 4095, 33] * 30
