@@ -383,3 +383,45 @@ def test_topk_general_many_tensors(kind, dgc, T):
         assert np.array_equal(bits(de[t].cpu().numpy()), bits(e[t])), t
         if dgc:
             assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), t
+
+
+@pytest.mark.timeout(600)
+@pytest.mark.parametrize("kind,dgc", [("topk", False), ("topk_sampled", False), ("topk_sampled", True)])
+@pytest.mark.parametrize("ns", [[34_000_001, 5], [9_000_001] + [5] * 260], ids=["34M", "9M+260"])
+def test_topk_general_long_tensor(kind, dgc, ns):
+    """A tensor of more chunks than the placing workgroup keeps in registers
+    (8 per thread, of 1024 threads or, above 256 tensors, 256), with the k-th
+    key among many close ones, so that chunks are counted again; at 34 M
+    elements the passes' accesses are non-temporal too.  Two steps against
+    the oracle, bit for bit."""
+    import torch
+    from paper_2205_14465_amd import binding as B
+    rng = np.random.default_rng(len(ns))
+    ratio, m = 0.01, 0.9
+    e = [np.zeros(n, np.float32) for n in ns]
+    u = [np.zeros(n, np.float32) for n in ns]
+    de, du = [torch_dev(x) for x in e], [torch_dev(x) for x in u]
+    out = B.alloc_payload(kind, ratio, ns)
+    ws = B.alloc_workspace(kind, ratio, ns, 1)
+    for step in range(2):
+        grads = [(rng.standard_normal(n) * 0.01).astype(np.float32) for n in ns]
+        n0 = ns[0]
+        # twice k values within 2^-9 of 1 in one stretch, and thinly all over
+        grads[0][n0 // 3:n0 // 3 + n0 // 100] = 1.0 + rng.random(n0 // 100, dtype=np.float32) * 2.0 ** -9
+        grads[0][::100] = -1.0 - rng.random(grads[0][::100].size, dtype=np.float32) * 2.0 ** -9
+        dg = [torch_dev(x) for x in grads]
+        with topk_path("general"):
+            if dgc:
+                B.bytecomp_compress_dgc(kind, ratio, step, m, dg, de, du, out, ws)
+                want, e, u = O.compress_dgc_set(kind, ratio, step, m, grads, e, u)
+            else:
+                B.bytecomp_compress(kind, ratio, step, dg, de, out, ws)
+                want, e = O.compress_set(kind, ratio, step, grads, e)
+        torch.cuda.synchronize()
+        total = int(want["off"][-1])
+        assert np.array_equal(out["idx"].cpu().numpy().view(np.uint32)[:total], want["idx"]), step
+        assert np.array_equal(bits(out["val"].cpu().numpy()[:total]), bits(want["val"])), step
+        for t in (0, 1, len(ns) - 1):
+            assert np.array_equal(bits(de[t].cpu().numpy()), bits(e[t])), (step, t)
+            if dgc:
+                assert np.array_equal(bits(du[t].cpu().numpy()), bits(u[t])), (step, t)
