@@ -84,9 +84,10 @@ __global__ __launch_bounds__(kBlock) void part_count(const PDesc* __restrict__ p
 // then a walk along the run (one tensor up to 256 tensors), from the thread's
 // position before if that lies in the run too.  The grid follows the entries
 // expected of the part: each workgroup reads every tensor's count and adds to
-// one counter (512 workgroups for 134 spans: 11 us, 135: 7 us).  Spans are 1024 positions, four per thread, or 4096 where
-// the part holds more than the grid covers so (entries crowded into one part,
-// high ratios: 5 M entries 55 us with the short spans).
+// one counter (512 workgroups for 134 spans: 11 us, 135: 7 us).  Spans are 1024
+// positions, four per thread, or 4096 where the part holds more than the grid
+// covers so (entries crowded into one part, high ratios: 5 M entries 55 us with
+// the short spans).
 constexpr uint32_t kPackSpan = 1024;
 
 namespace {

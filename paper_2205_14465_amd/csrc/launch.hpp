@@ -13,9 +13,11 @@
 
 namespace bc {
 
-// Pointers into the caller's workspace.  Every call clears the counters it
-// uses in its first kernel, so the workspace needs no initialisation and may
-// be shared by calls of different kinds and shapes (not concurrently).
+// Pointers into the caller's workspace: a header of 256 bytes that
+// bytecomp_workspace_init zeroes (its first word holds the failure flags, no
+// kernel uses the rest), then the regions of the call's kind, which every call
+// clears as far as it needs to: calls of different kinds and shapes may share a
+// workspace (not concurrently) and find anything in the regions.
 struct Ws {
     uint32_t* flags;        // header: failure flags
     // BC_SIGN1
@@ -138,8 +140,17 @@ struct CallRange {
     CallRange(const CallRange&) = delete;
     CallRange& operator=(const CallRange&) = delete;
 };
-// Top-k calls of at most this many chunks take the few-chunk path.
-constexpr uint32_t kTopkFewChunksMax = 2048;  // 8M elements: its counts fit in 31 bits
+// Top-k calls of at most this many chunks (8M elements) take the few-chunk
+// path.  The line was drawn when the general pipeline had sixteen launches; the
+// sampled kind's seven have moved the crossing below it.  us a call, few-chunk
+// path and general pipeline (exact kind, sampled kind):
+//   chunks        512 (450)          1024 (900)         1536 (1500)        2048 (1950)
+//   1 tensor      44   45  42        60   51  46        76   57  51        94   65  55
+//   16 tensors    33   42  39        38   48  44        47   54  49        58   61  53
+//   150 tensors   33   48  44        36   52  46        44   55  50        53   60  53
+// so the few-chunk path is the better one below about 500 chunks of one tensor
+// and 1600 of sixteen or more.
+constexpr uint32_t kTopkFewChunksMax = 2048;
 uint32_t topk_few_chunks_limit();
 
 // Launch `kernel`, bracketed by the requested events when kernel `k` is to
@@ -227,8 +238,9 @@ bool randk_buckets(uint32_t C, uint32_t* S, uint32_t* NB);
 
 // Divisible scheme: pack part j of one payload.  word_bits: 0 for the
 // sparse kinds, else the code bits per element (1 sign, 2, 4, 8); words:
-// the packed words (word kinds), max_words: the longest range's; expected: the part's entries (sparse) if
-// every tensor's were spread evenly, which sizes the copy grid.
+// the packed words (word kinds), max_words: the longest range's; expected: the
+// part's entries (sparse) if every tensor's were spread evenly, which sizes the
+// copy grid.
 hipError_t launch_pack_part(int word_bits, const PDesc* p, int T, bc_payload_dev in, bc_payload_dev out,
                             uint64_t* part_off, uint64_t words, uint64_t max_words, uint64_t expected, int cus,
                             hipStream_t s);
