@@ -261,10 +261,12 @@ WsPlan plan_workspace(int kind, int T, uint64_t C, uint64_t sum_k, bool agg_tabl
         size_t per = (size_t)topk_general_copies(T) * kBins0;
         if (C <= kTopkFewChunksMax && per < 4 * kBins0 + 2 * kBins12) per = 4 * kBins0 + 2 * kBins12;
         take(p.t_hist, t * per * 4);
-        // the words of few tensors on a page of their own, apart from the
-        // histograms' atomic additions (a call of 64 thousand elements: 27.0
-        // us, 27.3 right behind them)
-        if (T <= 256) at = (at + 4095) & ~(size_t)4095;
+        // the words of few tensors on a multiple of 16 KiB: the time of a call
+        // of 64 thousand elements, a chain of short kernels, depends on where
+        // they lie modulo that (memory is dealt to the stacks in 4 KiB pieces,
+        // by period four): 26.1 to 26.7 us in the first two quarters, 27.3 to
+        // 27.6 in the others
+        if (T <= 256) at = (at + 16383) & ~(size_t)16383;
         take(p.t_thr, t * 4);
         take(p.t_prefix, t * 4);
         take(p.t_krem, t * 4);
