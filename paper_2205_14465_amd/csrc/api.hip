@@ -261,11 +261,11 @@ WsPlan plan_workspace(int kind, int T, uint64_t C, uint64_t sum_k, bool agg_tabl
         size_t per = (size_t)topk_general_copies(T) * kBins0;
         if (C <= kTopkFewChunksMax && per < 4 * kBins0 + 2 * kBins12) per = 4 * kBins0 + 2 * kBins12;
         take(p.t_hist, t * per * 4);
-        // the words of few tensors on a multiple of 16 KiB: the time of a call
-        // of 64 thousand elements, a chain of short kernels, depends on where
-        // they lie modulo that (memory is dealt to the stacks in 4 KiB pieces,
-        // by period four): 26.1 to 26.7 us in the first two quarters, 27.3 to
-        // 27.6 in the others
+        // the words of few tensors on a multiple of 16 KiB: a call of 64 thousand
+        // elements, a chain of short kernels, takes up to 5% more or less with
+        // their place modulo that (memory is dealt out in 4 KiB pieces).  On one
+        // card 26.1 to 26.7 us in the first two quarters and 27.3 to 27.6 in
+        // the others, on another 27.2 to 27.7 in all four.
         if (T <= 256) at = (at + 16383) & ~(size_t)16383;
         take(p.t_thr, t * 4);
         take(p.t_prefix, t * 4);
